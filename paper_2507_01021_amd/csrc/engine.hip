@@ -1148,7 +1148,7 @@ class EngineT final : public Engine {
               const Epi& epi, hipStream_t s = nullptr) {
         if (!s) s = st_;
         if constexpr (std::is_same<T, bf16>::value) gemm_bf16(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, s);
-        else gemm_simt(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, s);
+        else gemm_f32(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, s);
     }
 
     // Encoder layer l over segments b0 .. b0 + nb - 1 of the pass, on stream
@@ -1173,8 +1173,8 @@ class EngineT final : public Engine {
             hipLaunchKernelGGL(enc_attn_bf16_kernel, dim3((N_CTX + ea::QB - 1) / ea::QB, nb * H_), dim3(256), 0, s,
                                qh, kh, vt, ob, H_, d);
         else
-            hipLaunchKernelGGL(enc_attn_f32_kernel, dim3((N_CTX + 63) / 64, nb * H_), dim3(64), 0, s, qh, kh, vt, ob,
-                               H_, d);
+            hipLaunchKernelGGL(enc_attn_f32_kernel, dim3((N_CTX + ef::QB - 1) / ef::QB, nb * H_), dim3(256), 0, s, qh,
+                               kh, vt, ob, H_, d);
         prof_end(WHISPER_K_ENC_ATTN, s);
         gemm(L.Wo, d, 0, ob, d, 0, d, M, d, 1, EpiResid{L.bo, x, d}, s);
         ln(x, zb, L.ln2g, L.ln2b, M, s);
@@ -1188,7 +1188,7 @@ class EngineT final : public Engine {
     template <class Epi>
     void proj(const T* W, int MA, const T* X, int n, int K, int KS, const Epi& epi, hipStream_t s) {
         if constexpr (std::is_same<T, bf16>::value) skinny_bf16(W, MA, X, n, K, KS, epi, s);
-        else gemm_simt(W, K, K / KS, X, K, K / KS, MA, n, K / KS, KS, epi, s);
+        else gemm_f32(W, K, K / KS, X, K, K / KS, MA, n, K / KS, KS, epi, s);
     }
     // residual projection: x += W X + bias (split-K partials), then z = LN(x)
     void proj_resid(const T* W, const T* X, int n, int K, int KS, const float* bias, const float* g, const float* b,

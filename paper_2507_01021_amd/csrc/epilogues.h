@@ -240,9 +240,28 @@ struct EpiCTC {
     const float* bias;
     float* out;
     int V;
-    __device__ EpiPre pre(int i, int, int) const { EpiPre p{}; p.a = ld4(bias + i); return p; }
+    __device__ EpiPre pre(int i, int, int) const {
+        EpiPre p{};
+        if ((V & 3) == 0) {
+            p.a = ld4(bias + i);
+        } else {
+            p.a.x = bias[i];
+            p.a.y = bias[min(i + 1, V - 1)];
+            p.a.z = bias[min(i + 2, V - 1)];
+            p.a.w = bias[min(i + 3, V - 1)];
+        }
+        return p;
+    }
     __device__ void operator()(int i, int j, int, float a, float b, float c, float e, const EpiPre& p) const {
-        st4(out + (long long)j * V + i, a + p.a.x, b + p.a.y, c + p.a.z, e + p.a.w);
+        float* o = out + (long long)j * V + i;
+        if ((V & 3) == 0) {
+            st4(o, a + p.a.x, b + p.a.y, c + p.a.z, e + p.a.w);
+            return;
+        }
+        o[0] = a + p.a.x;  // rows beyond n_vocab are dropped
+        if (i + 1 < V) o[1] = b + p.a.y;
+        if (i + 2 < V) o[2] = c + p.a.z;
+        if (i + 3 < V) o[3] = e + p.a.w;
     }
 };
 

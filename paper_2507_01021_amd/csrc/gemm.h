@@ -17,8 +17,8 @@
 //   3-stage ring (two workgroups per CU), for K <= 1024. Tiles are mapped to
 //   the XCDs so that workgroups sharing an L2 share operand tiles.
 //   Requires K % 64 == 0, MA % 4 == 0, 16-byte aligned rows (lda, ldb % 8 == 0).
-// gemm_simt: fp32 (or bf16 storage) SIMT kernel for the fp32 model: 64x64x16
-//   tile, 4x4 outputs per thread, any K, any lda.
+// gemm_f32: fp32 inputs on v_mfma_f32_16x16x4_f32 for the fp32 model, 64x64 or
+//   128x128 tiles. Requires K % 32 == 0 and 16-byte aligned rows.
 #pragma once
 
 #include <atomic>
@@ -71,17 +71,17 @@ __device__ inline void xcd_tile(int bid, int tilesA, int tilesB, int& ta, int& t
     ta = g * GA + (w - tb * ga);
 }
 
-// Epilogue of a wave's NI x 4 blocks of 16 x 16 results: lane (fr, fc) of
+// Epilogue of a wave's NI x NJ blocks of 16 x 16 results: lane (fr, fc) of
 // block (i, j) holds rows ia + 16 i + 4 fc .. + 3 of column jb + 16 j + fr.
 // For each column block, all of its loads (pre) are issued before its
 // stores. A tile wholly inside the output (full, the common case) skips the
 // per-element bounds tests, each a branch and an exec-mask update.
-template <int NI, class Epi>
-__device__ __forceinline__ void tile_epilogue(const Epi& epi, const mfma_f32x4 (&acc)[NI][4], int ia, int jb, int fr,
+template <int NI, int NJ, class Epi>
+__device__ __forceinline__ void tile_epilogue(const Epi& epi, const mfma_f32x4 (&acc)[NI][NJ], int ia, int jb, int fr,
                                               int fc, int z, int MA, int MB, bool full) {
     if (full) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             const int jj = jb + j * 16 + fr;
             EpiPre pre[NI];
 #pragma unroll
@@ -93,7 +93,7 @@ __device__ __forceinline__ void tile_epilogue(const Epi& epi, const mfma_f32x4 (
         return;
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NJ; ++j) {
         const int jj = jb + j * 16 + fr;
         const bool jok = jj < MB;
         EpiPre pre[NI];
@@ -309,66 +309,121 @@ inline void gemm_bf16(const bf16* A, int lda, long long sA, const bf16* B, int l
                        sA, B, ldb, sB, MA, MB, K, tilesA, epi);
 }
 
-// ----------------------------------------------------------------- SIMT fp32
+// ----------------------------------------------------------------- fp32 MFMA
+//
+// C = A B^T in fp32 on v_mfma_f32_16x16x4_f32 (fp32 products and sums): a
+// workgroup tile of 32 WT x 32 WT, 4 waves of 16 WT x 16 WT, K tiles of 32
+// streamed into an LDS ring of NS stages with direct global->LDS loads.
+// A lane reads 16 bytes (four k) of a row per fragment and the four values
+// feed four MFMAs, so MFMA step r reduces over k = 4 (lane / 16) + r of a
+// 16-wide slice in both operands. LDS rows are 128 bytes; the 16-byte chunk c
+// of row r sits at c ^ ((r >> 1) & 7), so the 16 rows of one read pass fill
+// the 64 banks once.
+// Bound by the fp32 matrix rate (each 16x16x4 takes 32 cycles of a SIMD): a
+// fragment read pair feeds 4 WT MFMAs, so LDS and L2 are far from their
+// limits with either tile. 13500 x 1536 x 384 with GELU: 153 us (104 TFLOP/s;
+// with vector FMAs 10500 rows took 374 us, 33 TFLOP/s); 1500 x 1536 x 384:
+// 29 us (vector FMAs 74 us).
+namespace gf {
+constexpr int BK = 32;
+}
 
-template <class TA, class TB, class Epi>
-__global__ __launch_bounds__(256) void gemm_simt_kernel(const TA* __restrict__ A, int lda, long long sA,
-                                                        const TB* __restrict__ B, int ldb, long long sB,
-                                                        int MA, int MB, int K, Epi epi) {
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64 + 4];
+template <int WT, int NS, class Epi>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restrict__ A, int lda, long long sA,
+                                                          const float* __restrict__ B, int ldb, long long sB, int MA,
+                                                          int MB, int K, int tilesA, Epi epi) {
+    constexpr int TB = 32 * WT, OP_BYTES = TB * 128, STAGE = 2 * OP_BYTES;
+    extern __shared__ __align__(16) unsigned char lds[];
     const int z = blockIdx.z;
     A += (long long)z * sA;
     B += (long long)z * sB;
-    const int a0 = blockIdx.x * 64, b0 = blockIdx.y * 64;
-    const int t = threadIdx.x;
-    const int ag = t & 15, bgp = t >> 4;  // this thread's 4 A rows and 4 B rows
-    float acc[4][4] = {};
-    const int lr = t >> 2, lk = (t & 3) * 4;  // loader: row lr, k lk..lk+3
-    const long long rowA = min(a0 + lr, MA - 1), rowB = min(b0 + lr, MB - 1);
-    for (int k0 = 0; k0 < K; k0 += 16) {
+    int ta, tb;
+    xcd_tile(blockIdx.x, tilesA, (int)(gridDim.x / tilesA), ta, tb);
+    const int a0 = ta * TB, b0 = tb * TB;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wa = (wave & 1) * 16 * WT, wb = (wave >> 1) * 16 * WT;
+    const int fr = lane & 15, fc = lane >> 4;
+
+    // Direct loads: wave w fills rows 8 WT w .. 8 WT (w + 1) - 1 of both tiles
+    // with WT + WT instructions of 8 rows; lane i loads the logical chunk
+    // stored at position i % 8 of row i / 8.
+    const float* ga[4];  // WT of them
+    const float* gp[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int k = k0 + lk + q;
-            As[lk + q][lr] = k < K ? ldf(A + rowA * lda + k) : 0.f;
-            Bs[lk + q][lr] = k < K ? ldf(B + rowB * ldb + k) : 0.f;
+    for (int s = 0; s < WT; ++s) {
+        const int r = wave * 8 * WT + s * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        ga[s] = A + (long long)min(a0 + r, MA - 1) * lda + c * 4;
+        gp[s] = B + (long long)min(b0 + r, MB - 1) * ldb + c * 4;
+    }
+#define WMI_ISSUEF(KT)                                                                                    \
+    do {                                                                                                  \
+        int sa_ = ((KT) % NS) * STAGE + wave * 8 * WT * 128, sb_ = sa_ + OP_BYTES;                        \
+        const int k_ = (KT) * gf::BK;                                                                     \
+        _Pragma("unroll") for (int s = 0; s < WT; ++s) {                                                 \
+            __builtin_amdgcn_global_load_lds(ga[s] + k_, lds + sa_ + s * 1024, 16, 0, 0);                 \
+            __builtin_amdgcn_global_load_lds(gp[s] + k_, lds + sb_ + s * 1024, 16, 0, 0);                 \
+        }                                                                                                 \
+    } while (0)
+    mfma_f32x4 acc[WT][WT];
+#pragma unroll
+    for (int i = 0; i < WT; ++i)
+#pragma unroll
+        for (int j = 0; j < WT; ++j) acc[i][j] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int nk = K / gf::BK;
+#pragma unroll
+    for (int q = 0; q < NS - 1; ++q)
+        if (q < nk) WMI_ISSUEF(q);
+    for (int kt = 0; kt < nk; ++kt) {
+        // tile kt has landed once only the later tiles' 2 WT loads are pending
+        const int later = min(nk - 1 - kt, NS - 2);
+        static_assert((WT == 2 && NS <= 4) || NS == 2, "the waits below are literals");
+        if (later >= 2) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(8));
+        else if (later == 1) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(4));
+        else __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
+        __builtin_amdgcn_s_barrier();
+        if (kt + NS - 1 < nk) WMI_ISSUEF(kt + NS - 1);
+        const unsigned char* stage = lds + (kt % NS) * STAGE;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            mfma_f32x4 fa[WT], fb[WT];
+#pragma unroll
+            for (int i = 0; i < WT; ++i) {
+                const int ra = wa + i * 16 + fr, rb = wb + i * 16 + fr, c = 4 * h + fc;
+                fa[i] = *reinterpret_cast<const mfma_f32x4*>(stage + ra * 128 + ((c ^ ((ra >> 1) & 7)) << 4));
+                fb[i] = *reinterpret_cast<const mfma_f32x4*>(stage + OP_BYTES + rb * 128 + ((c ^ ((rb >> 1) & 7)) << 4));
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < WT; ++j)
+#pragma unroll
+                    for (int i = 0; i < WT; ++i)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][r], fb[j][r], acc[i][j], 0, 0, 0);
         }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            float a[4], b[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) { a[q] = As[k][ag * 4 + q]; b[q] = Bs[k][bgp * 4 + q]; }
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-#pragma unroll
-                for (int y = 0; y < 4; ++y) acc[x][y] = fmaf(a[x], b[y], acc[x][y]);
-        }
-        __syncthreads();
     }
-    const int ii = a0 + ag * 4;
-    if (ii >= MA) return;
-    EpiPre pre[4];
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-        const int jj = b0 + bgp * 4 + y;
-        if (jj < MB) pre[y] = epi.pre(ii, jj, z);
-    }
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-        const int jj = b0 + bgp * 4 + y;
-        if (jj < MB) epi(ii, jj, z, acc[0][y], acc[1][y], acc[2][y], acc[3][y], pre[y]);
-    }
+#undef WMI_ISSUEF
+    tile_epilogue(epi, acc, a0 + wa, b0 + wb, fr, fc, z, MA, MB, a0 + TB <= MA && b0 + TB <= MB);
 }
 
-template <class TA, class TB, class Epi>
-inline void gemm_simt(const TA* A, int lda, long long sA, const TB* B, int ldb, long long sB, int MA,
-                      int MB, int K, int batch, const Epi& epi, hipStream_t st) {
+template <class Epi>
+inline void gemm_f32(const float* A, int lda, long long sA, const float* B, int ldb, long long sB, int MA, int MB,
+                     int K, int batch, const Epi& epi, hipStream_t st) {
     // rows i0..i0+3 past MA reach the epilogue when MA % 4 != 0: it must drop them
-    if (MA <= 0 || MB <= 0 || K <= 0 || batch <= 0) throw ArgError(-1, "gemm_simt: unsupported shape");
-    dim3 grid((MA + 63) / 64, (MB + 63) / 64, batch);
-    hipLaunchKernelGGL((gemm_simt_kernel<TA, TB, Epi>), grid, dim3(256), 0, st, A, lda, sA, B, ldb, sB,
-                       MA, MB, K, epi);
+    if (MA <= 0 || MB <= 0 || K <= 0 || K % gf::BK || lda % 4 || ldb % 4 || sA % 4 || sB % 4 || batch <= 0)
+        throw ArgError(-1, "gemm_f32: unsupported shape");
+    // 128 x 128 tiles once they fill the chip's 512 workgroup slots (two per
+    // CU); below that the 64 x 64 tiles' four times as many workgroups.
+    const int t128a = (MA + 127) / 128, t128b = (MB + 127) / 128;
+    if ((long long)t128a * t128b * batch >= 512) {
+        hipLaunchKernelGGL((gemm_f32_kernel<4, 2, Epi>), dim3(t128a * t128b, 1, batch), dim3(256), 2 * 2 * 128 * 128, st,
+                           A, lda, sA, B, ldb, sB, MA, MB, K, t128a, epi);
+    } else {
+        const int ta = (MA + 63) / 64, tb = (MB + 63) / 64;
+        hipLaunchKernelGGL((gemm_f32_kernel<2, 4, Epi>), dim3(ta * tb, 1, batch), dim3(256), 4 * 2 * 64 * 128, st, A,
+                           lda, sA, B, ldb, sB, MA, MB, K, ta, epi);
+    }
 }
 
 }  // namespace wmi
