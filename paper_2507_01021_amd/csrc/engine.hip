@@ -18,8 +18,8 @@
 //   1500 cached encoder positions, output projection +
 //   residual, LN, fc1 + GELU, fc2 + residual -> final LN -> logits against
 //   the token embedding -> argmax, next input, position advance.
-//   In bf16 the projection weights and the activations they multiply are
-//   fragment-major (frag_off). With 32 or more slots in bf16 the rows are
+//   The projection weights and the activations they multiply are
+//   fragment-major (dec_off). With 32 or more slots in bf16 the rows are
 //   split in two halves (the first a whole number of 16-row tiles) that run
 //   the complete step on two streams, each as its own captured graph (the
 //   halves touch disjoint slots), so the two chains of small latency-bound
@@ -540,9 +540,8 @@ class EngineT final : public Engine {
         run_step(b, n, want_logits, s);
     }
 
-    // Buffers of one step's rows: the decoder rows, the logits (fp32 model:
-    // always written; bf16: when asked for), greedy-choice keys, tokens out
-    // and forced tokens in (or null).
+    // Buffers of one step's rows: the decoder rows, the logits (written when
+    // asked for), greedy-choice keys, tokens out and forced tokens in (or null).
     struct StepBufs {
         RowBufs rows;
         float* logits;
@@ -560,14 +559,8 @@ class EngineT final : public Engine {
         float* logits = sb.logits;
         unsigned long long* keys = sb.keys;
         const TokenFilter tf{use_never_ ? never_mask_ : nullptr, use_first_ ? first_mask_ : nullptr, list, pos_, npr_};
-        int nk = ARGMAX_CHUNKS;
-        if constexpr (std::is_same<T, bf16>::value) {
-            // the head kernel keeps one key per row and workgroup; logits only when asked for
-            nk = head_argmax(tok_emb_, V_, b.dz, n, d, HeadArgs{want_logits ? logits : nullptr, keys, V_, tf}, s);
-        } else {
-            proj(tok_emb_, V_, b.dz, n, d, 1, EpiLogits{logits, V_}, s);
-            hipLaunchKernelGGL(argmax_keys_kernel, dim3(ARGMAX_CHUNKS, n), dim3(256), 0, s, logits, V_, keys, tf);
-        }
+        // the head kernel keeps one key per row and workgroup; logits only when asked for
+        const int nk = head_argmax(tok_emb_, V_, b.dz, n, d, HeadArgs{want_logits ? logits : nullptr, keys, V_, tf}, s);
         hipLaunchKernelGGL(argmax_step_kernel, dim3(n), dim3(64), 0, s, keys, nk, list, pos_, npr_, seq_, gen_,
                            sb.forced, sb.outtok, eot_, stop_at_, dec_err_);
     }
@@ -592,6 +585,7 @@ class EngineT final : public Engine {
         L.dh = take(n16 * 4 * d * sizeof(T));
         L.part = take((size_t)KSMAX * n * d * sizeof(float));
         L.keys = take((size_t)n * nkeys_ * sizeof(unsigned long long));
+        // the documented capacity of the fp32 model counts the rows' logits
         L.logits = std::is_same<T, bf16>::value ? o : take((size_t)n * V_ * sizeof(float));
         L.end = o;
         return L;
@@ -984,7 +978,7 @@ class EngineT final : public Engine {
     T *kts_, *vs_, *ktc_, *vc_, *dz_, *dq_, *datt_, *dh_;
     float *dx_, *logits_, *gpart_;
     unsigned long long* keys_;  // greedy-choice keys [S][nkeys_]
-    int nkeys_ = ARGMAX_CHUNKS;
+    int nkeys_ = 16;
     int* dec_err_;              // set by a decode step that found no admissible token
     std::vector<int> list_host_;
     bool graphs_ = true, split_ = true, fused_ln_ = true;
@@ -1187,8 +1181,7 @@ class EngineT final : public Engine {
     // decode projection: rows = weight rows (MA), n activation rows of width K
     template <class Epi>
     void proj(const T* W, int MA, const T* X, int n, int K, int KS, const Epi& epi, hipStream_t s) {
-        if constexpr (std::is_same<T, bf16>::value) skinny_bf16(W, MA, X, n, K, KS, epi, s);
-        else gemm_f32(W, K, K / KS, X, K, K / KS, MA, n, K / KS, KS, epi, s);
+        skinny(W, MA, X, n, K, KS, epi, s);
     }
     // residual projection: x += W X + bias (split-K partials), then z = LN(x)
     void proj_resid(const T* W, const T* X, int n, int K, int KS, const float* bias, const float* g, const float* b,
@@ -1336,27 +1329,24 @@ class EngineT final : public Engine {
             return q;
         };
         // Decoder projection matrices with K columns (rows of the named tensors
-        // stacked) in the decoder layout: bf16 fragment-major with the rows
-        // padded with zeros to a multiple of 32, fp32 row-major.
+        // stacked) in the decoder's fragment-major layout, the rows padded with
+        // zeros to a multiple of 32.
         auto dec_mat = [&](const std::vector<std::string>& names, int K) -> T* {
-            if constexpr (!std::is_same<T, bf16>::value) {
-                return cat(names);
-            } else {
-                size_t rows = 0;
-                for (auto& nme : names) rows += count(nme) / K;
-                std::vector<T> h((rows + 31) / 32 * 32 * K);
-                memset(h.data(), 0, h.size() * sizeof(T));
-                size_t r0 = 0;
-                for (auto& nme : names) {
-                    const T* src = raw(nme);
-                    const size_t nr = count(nme) / K;
-                    for (size_t r = 0; r < nr; ++r)
-                        for (int k = 0; k < K; k += 8)
-                            memcpy(&h[frag_off(r0 + r, k, K)], src + r * K + k, 8 * sizeof(T));
-                    r0 += nr;
-                }
-                return upload_new(h);
+            constexpr int EL = 16 / sizeof(T);
+            size_t rows = 0;
+            for (auto& nme : names) rows += count(nme) / K;
+            std::vector<T> h((rows + 31) / 32 * 32 * K);
+            memset(h.data(), 0, h.size() * sizeof(T));
+            size_t r0 = 0;
+            for (auto& nme : names) {
+                const T* src = raw(nme);
+                const size_t nr = count(nme) / K;
+                for (size_t r = 0; r < nr; ++r)
+                    for (int k = 0; k < K; k += EL)
+                        memcpy(&h[dec_off<T>(r0 + r, k, K)], src + r * K + k, EL * sizeof(T));
+                r0 += nr;
             }
+            return upload_new(h);
         };
         const int d = d_;
         {  // conv kernels to [out][tap][in] (input channels of conv1 padded to CP)
@@ -1487,7 +1477,7 @@ class EngineT final : public Engine {
             if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev_) == hipSuccess && khz > 0)
                 wall_khz_ = khz;
         }
-        nkeys_ = std::max(ARGMAX_CHUNKS, (V_ + 31) / 32);
+        nkeys_ = std::max(16, (V_ + 31) / 32);
         keys_ = dalloc<unsigned long long>(S * (size_t)nkeys_);
         dec_err_ = dalloc<int>(1);
         if (prefill_) {

@@ -265,20 +265,4 @@ struct EpiCTC {
     }
 };
 
-struct EpiLogits {  // out[r][i..i+3] (fp32), rows beyond n_vocab dropped
-    float* out;
-    int V;
-    __device__ EpiPre pre(int, int, int) const { return EpiPre{}; }
-    __device__ void operator()(int i, int r, int, float a, float b, float c, float e, const EpiPre&) const {
-        float* p = out + (long long)r * V + i;
-        if (i + 3 < V) {
-            p[0] = a; p[1] = b; p[2] = c; p[3] = e;
-        } else {
-            if (i < V) p[0] = a;
-            if (i + 1 < V) p[1] = b;
-            if (i + 2 < V) p[2] = c;
-        }
-    }
-};
-
 }  // namespace wmi

@@ -1129,47 +1129,68 @@ __global__ void stamp_reset_kernel(unsigned long long* __restrict__ s, int n) {
     }
 }
 
-// ------------------------------------------------------------- skinny decode GEMM (bf16 MFMA)
+// ------------------------------------------------------------- skinny decode GEMM (MFMA)
 //
 // C[i][r] = sum_k W[i][k] X[r][k] for a few rows r (active decode slots,
 // n <= 16 * NT) and many weight rows i: each weight byte is read once.
-// W and X are fragment-major (frag_off), so every load below reads 1 KiB
-// contiguous. Grid (row tiles, KS): workgroup (tile, ks) covers 16 * RT
+// W and X are fragment-major (dec_off), so every load below reads 1 KiB
+// contiguous; a k-step is KSTEP<T> columns: one 16x16x32 MFMA in bf16, four
+// 16x16x4 MFMAs in fp32. Grid (row tiles, KS): workgroup (tile, ks) covers 16 * RT
 // weight rows and reduction columns [ks * Kc, (ks + 1) * Kc). Its 4 waves
-// take interleaved 32-wide k-steps, U steps' loads issued before their
+// take interleaved k-steps, U steps' loads issued before their
 // MFMAs; the wave partial sums are added in LDS in a fixed order, so a row's
 // result never depends on which other rows are present (row tiles past n
-// re-read the last valid tile and are dropped). NW waves per workgroup
+// re-read the last valid tile and are dropped). The fp32 model's projections
+// took 37 us each (d = 384, 7 rows) as a GEMM of 64 x 64 vector-FMA tiles and
+// 12 us on its MFMA tiles; here 3.4-3.8 us, a launch's latency. NW waves per workgroup
 // (4, or more for long reductions), red: (NW - 1) * RT * NT * 4 * 64 floats.
-template <int RT, int NT, int U, int NW = 4>
-__device__ __forceinline__ void skinny_core(const bf16* __restrict__ W, const bf16* __restrict__ X, int nks_tot, int n,
+template <class T> struct Frag;  // 16 bytes of an operand per lane
+template <> struct Frag<bf16> {
+    typedef mfma_bf16x8 type;
+    static __device__ __forceinline__ mfma_f32x4 mma(type a, type b, mfma_f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct Frag<float> {
+    typedef mfma_f32x4 type;
+    static __device__ __forceinline__ mfma_f32x4 mma(type a, type b, mfma_f32x4 c) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], c, 0, 0, 0);
+        return c;
+    }
+};
+
+template <class T, int RT, int NT, int U, int NW = 4>
+__device__ __forceinline__ void skinny_core(const T* __restrict__ W, const T* __restrict__ X, int nks_tot, int n,
                                             int Kc, float* red, float (&v)[RT][NT][4]) {
+    typedef typename Frag<T>::type frag;
+    constexpr int EL = 16 / sizeof(T);  // elements of a lane's fragment
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int s_base = blockIdx.y * (Kc >> 5);
-    const bf16* wp[RT];
+    const int s_base = blockIdx.y * (Kc / KSTEP<T>);
+    const T* wp[RT];
 #pragma unroll
-    for (int t = 0; t < RT; ++t) wp[t] = W + (((long long)(blockIdx.x * RT + t) * nks_tot + s_base) * 64 + lane) * 8;
+    for (int t = 0; t < RT; ++t) wp[t] = W + (((long long)(blockIdx.x * RT + t) * nks_tot + s_base) * 64 + lane) * EL;
     const int ulast = (n - 1) >> 4;
-    const bf16* xp[NT];
+    const T* xp[NT];
 #pragma unroll
-    for (int u = 0; u < NT; ++u) xp[u] = X + (((long long)min(u, ulast) * nks_tot + s_base) * 64 + lane) * 8;
+    for (int u = 0; u < NT; ++u) xp[u] = X + (((long long)min(u, ulast) * nks_tot + s_base) * 64 + lane) * EL;
     mfma_f32x4 acc[RT][NT];
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int u = 0; u < NT; ++u) acc[t][u] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-    const int nks = Kc >> 5;
+    const int nks = Kc / KSTEP<T>;
     // Batches of U k-steps (s, s + NW, ...): all loads of a batch are issued
     // before its MFMAs; steps past the end re-read the last step and are skipped.
     for (int s0 = wave; s0 < nks; s0 += NW * U) {
-        mfma_bf16x8 a[U][RT], b[U][NT];
+        frag a[U][RT], b[U][NT];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int off = min(s0 + NW * q, nks - 1) * 512;
+            const int off = min(s0 + NW * q, nks - 1) * 64 * EL;
 #pragma unroll
-            for (int t = 0; t < RT; ++t) a[q][t] = *reinterpret_cast<const mfma_bf16x8*>(wp[t] + off);
+            for (int t = 0; t < RT; ++t) a[q][t] = *reinterpret_cast<const frag*>(wp[t] + off);
 #pragma unroll
-            for (int u = 0; u < NT; ++u) b[q][u] = *reinterpret_cast<const mfma_bf16x8*>(xp[u] + off);
+            for (int u = 0; u < NT; ++u) b[q][u] = *reinterpret_cast<const frag*>(xp[u] + off);
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
@@ -1178,7 +1199,7 @@ __device__ __forceinline__ void skinny_core(const bf16* __restrict__ W, const bf
                 for (int t = 0; t < RT; ++t)
 #pragma unroll
                     for (int u = 0; u < NT; ++u)
-                        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q][t], b[q][u], acc[t][u], 0, 0, 0);
+                        acc[t][u] = Frag<T>::mma(a[q][t], b[q][u], acc[t][u]);
             }
         }
     }
@@ -1210,9 +1231,9 @@ __device__ __forceinline__ void skinny_core(const bf16* __restrict__ W, const bf
 
 // Plain epilogue variant: wave 0 hands rows i..i+3 of column r to epi (its
 // loads, pre(), are issued before the main loop). z = ks.
-template <int RT, int NT, int U, class Epi, int NW = 4>
-__global__ __launch_bounds__(64 * NW) void skinny_bf16_kernel(const bf16* __restrict__ W, const bf16* __restrict__ X,
-                                                              int nks_tot, int MA, int n, int Kc, Epi epi) {
+template <class T, int RT, int NT, int U, class Epi, int NW = 4>
+__global__ __launch_bounds__(64 * NW) void skinny_kernel(const T* __restrict__ W, const T* __restrict__ X,
+                                                         int nks_tot, int MA, int n, int Kc, Epi epi) {
     __shared__ float red[(NW - 1) * RT * NT * 4 * 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int fr = lane & 15, fc = lane >> 4;
@@ -1228,7 +1249,7 @@ __global__ __launch_bounds__(64 * NW) void skinny_bf16_kernel(const bf16* __rest
             }
     }
     float v[RT][NT][4];
-    skinny_core<RT, NT, U, NW>(W, X, nks_tot, n, Kc, red, v);
+    skinny_core<T, RT, NT, U, NW>(W, X, nks_tot, n, Kc, red, v);
     if (wave > 0) return;
 #pragma unroll
     for (int t = 0; t < RT; ++t)
@@ -1423,9 +1444,9 @@ constexpr int skinny_u(int nks, int NT) {
          : (nks + 3) / 4 <= 6 ? 6 : 10;
 }
 
-#define WMI_SKINNY_U(Kc, NT, LAUNCH)                                                  \
+#define WMI_SKINNY_U(nks, NT, LAUNCH)                                                 \
     do {                                                                             \
-        const int u_ = skinny_u((Kc) / 32, NT);                                       \
+        const int u_ = skinny_u(nks, NT);                                             \
         if (u_ == 1) { constexpr int U = 1; LAUNCH; }                                 \
         else if (u_ == 2) { constexpr int U = 2; LAUNCH; }                            \
         else if (u_ == 3) { constexpr int U = 3; LAUNCH; }                            \
@@ -1482,7 +1503,7 @@ inline void skinny_resid(const bf16* W, int d, const bf16* X, int n, int K, cons
         auto launch = [&](auto nt) {
             constexpr int NT = decltype(nt)::value;
             WMI_RESID_U(nks, RESID_NW, NT,
-                        hipLaunchKernelGGL((skinny_bf16_kernel<1, NT, U, EpiResidX, RESID_NW>), grid,
+                        hipLaunchKernelGGL((skinny_kernel<bf16, 1, NT, U, EpiResidX, RESID_NW>), grid,
                                            dim3(64 * RESID_NW), 0, st, W, Xr, nks, d, m, K, epi));
         };
         if (m <= 16) launch(std::integral_constant<int, 1>{});
@@ -1505,21 +1526,15 @@ inline void skinny_ln(const bf16* W, int MA, const float* x, int n, int d, const
                                        st, W, x, g, b, MA, n, epi));
 }
 
-// W: fragment-major [MA rounded up to 32][K], X: fragment-major [n rounded up
+// W: fragment-major [MA rounded up to 16][K], X: fragment-major [n rounded up
 // to 16][K]; KS workgroups split K.
-template <class Epi>
-inline void skinny_bf16(const bf16* W, int MA, const bf16* X, int n, int K, int KS, const Epi& epi, hipStream_t st) {
-    if (KS < 1 || K % (32 * KS) || n <= 0 || n > 128 || MA <= 0) throw ArgError(-1, "skinny_bf16: unsupported shape");
-    const int Kc = K / KS, nks_tot = K / 32;
-    if (MA >= 16384) {  // output head: 32 rows per workgroup
-        const dim3 grid((MA + 31) / 32, KS);
-        WMI_SKINNY_NT(n, WMI_SKINNY_U(Kc, NT, hipLaunchKernelGGL((skinny_bf16_kernel<2, NT, U, Epi>), grid, dim3(256),
-                                                                0, st, W, X, nks_tot, MA, n, Kc, epi)));
-    } else {
-        const dim3 grid((MA + 15) / 16, KS);
-        WMI_SKINNY_NT(n, WMI_SKINNY_U(Kc, NT, hipLaunchKernelGGL((skinny_bf16_kernel<1, NT, U, Epi>), grid, dim3(256),
-                                                                0, st, W, X, nks_tot, MA, n, Kc, epi)));
-    }
+template <class T, class Epi>
+inline void skinny(const T* W, int MA, const T* X, int n, int K, int KS, const Epi& epi, hipStream_t st) {
+    if (KS < 1 || K % (KSTEP<T> * KS) || n <= 0 || n > 128 || MA <= 0) throw ArgError(-1, "skinny: unsupported shape");
+    const int Kc = K / KS, nks_tot = K / KSTEP<T>;
+    const dim3 grid((MA + 15) / 16, KS);
+    WMI_SKINNY_NT(n, WMI_SKINNY_U(Kc / KSTEP<T>, NT, hipLaunchKernelGGL((skinny_kernel<T, 1, NT, U, Epi>), grid,
+                                                                        dim3(256), 0, st, W, X, nks_tot, MA, n, Kc, epi)));
 }
 
 // ------------------------------------------------------------- CTC greedy decoding
@@ -1841,10 +1856,8 @@ __global__ __launch_bounds__(64) void ctc_beam_kernel(const float* __restrict__ 
 // candidate id i with logit v becomes the 64-bit key (order-preserving bits
 // of v << 32 | ~i): the largest key has the largest value and, among equal
 // values, the lowest id, whatever order keys are compared in. (1) Partial
-// maxima: in the bf16 model the output head's own kernel reduces its
-// workgroup's 32 ids per row and writes one key per (row, workgroup)
-// (head_argmax_kernel, below the decode projections); the fp32 model writes
-// its logits and argmax_keys_kernel reduces ARGMAX_CHUNKS chunks per row.
+// maxima: the output head's own kernel reduces its workgroup's 32 ids per
+// row and writes one key per (row, workgroup) (head_argmax_kernel below).
 // (2) argmax_step_kernel: one wave per row takes the largest of the row's
 // keys, records the token, feeds it (or the forced token) as the next input
 // once the prompt is consumed, and advances the slot's position.
@@ -1853,8 +1866,6 @@ __global__ __launch_bounds__(64) void ctc_beam_kernel(const float* __restrict__ 
 // is at its first generated token when its input is the prompt's last).
 // A row with no admissible key (every id filtered, which the API refuses,
 // or keys lost to non-numbers) records token 0 and raises *err.
-constexpr int ARGMAX_CHUNKS = 16;
-
 struct TokenFilter {
     const unsigned* never;  // [V / 32 + 1] bit mask, or null
     const unsigned* first;  // [V / 32 + 1] bit mask, or null
@@ -1874,49 +1885,6 @@ __host__ __device__ inline int key_token(unsigned long long k, int* bad) {
         return 0;
     }
     return (int)(0xffffffffu - (unsigned)(k & 0xffffffffull));
-}
-
-// fp32 model: keys[r][chunk] = the largest key of chunk `chunk` of row r's logits.
-__global__ __launch_bounds__(256) void argmax_keys_kernel(const float* __restrict__ logits, int V,
-                                                          unsigned long long* __restrict__ keys, TokenFilter f) {
-    const int r = blockIdx.y, t = threadIdx.x;
-    const int per = (V + ARGMAX_CHUNKS - 1) / ARGMAX_CHUNKS;
-    const int lo = blockIdx.x * per, hi = min(V, lo + per);
-    const float* lg = logits + (long long)r * V;
-    const unsigned* never = f.never;
-    const unsigned* first = nullptr;
-    if (f.first) {
-        const int s = f.list[r];
-        if (f.pos[s] == f.n_prompt[s] - 1) first = f.first;
-    }
-    unsigned long long k = 0;
-    for (int i = lo + t; i < hi; i += 256 * 4) {
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = (i + 256 * q < hi) ? lg[i + 256 * q] : 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int j = i + 256 * q;
-            if (j >= hi) continue;
-            const unsigned bit = 1u << (j & 31);
-            if ((never && (never[j >> 5] & bit)) || (first && (first[j >> 5] & bit))) continue;
-            const unsigned long long c = amax_key(v[q], j);
-            k = c > k ? c : k;
-        }
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long c = __shfl_xor(k, o, 64);
-        k = c > k ? c : k;
-    }
-    __shared__ unsigned long long sk[4];
-    if ((t & 63) == 0) sk[t >> 6] = k;
-    __syncthreads();
-    if (t == 0) {
-        unsigned long long m = sk[0];
-        for (int w = 1; w < 4; ++w) m = sk[w] > m ? sk[w] : m;
-        keys[(long long)r * ARGMAX_CHUNKS + blockIdx.x] = m;
-    }
 }
 
 // eot >= 0: the first time a slot's generated token is eot, stop_at[slot]
@@ -1968,7 +1936,7 @@ __global__ __launch_bounds__(64) void argmax_step_kernel(const unsigned long lon
     pos[s] = p + 1;
 }
 
-// Output head with the first stage of the greedy choice (bf16 model): the
+// Output head with the first stage of the greedy choice: the
 // decode projection of the tied token embedding (RT = 2: 32 vocabulary rows
 // per workgroup), then, per activation row, the largest key (amax_key) over
 // the workgroup's admissible ids, written to keys[row][blockIdx.x]; the
@@ -1982,8 +1950,8 @@ struct HeadArgs {
     TokenFilter f;
 };
 
-template <int NT, int U>
-__global__ __launch_bounds__(256) void head_argmax_kernel(const bf16* __restrict__ W, const bf16* __restrict__ X,
+template <class T, int NT, int U>
+__global__ __launch_bounds__(256) void head_argmax_kernel(const T* __restrict__ W, const T* __restrict__ X,
                                                           int nks_tot, int n, int Kc, HeadArgs h) {
     constexpr int RT = 2;
     __shared__ float red[3 * RT * NT * 4 * 64];
@@ -2013,7 +1981,7 @@ __global__ __launch_bounds__(256) void head_argmax_kernel(const bf16* __restrict
         }
     }
     float v[RT][NT][4];
-    skinny_core<RT, NT, U>(W, X, nks_tot, n, Kc, red, v);
+    skinny_core<T, RT, NT, U>(W, X, nks_tot, n, Kc, red, v);
     if (wave > 0) return;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
@@ -2048,11 +2016,12 @@ __global__ __launch_bounds__(256) void head_argmax_kernel(const bf16* __restrict
 // Output head + per-workgroup keys for n rows (W: fragment-major [V rounded
 // up to 32][K], X fragment-major [n rounded up to 16][K]); returns the number
 // of keys per row.
-inline int head_argmax(const bf16* W, int V, const bf16* X, int n, int K, const HeadArgs& h, hipStream_t st) {
+template <class T>
+inline int head_argmax(const T* W, int V, const T* X, int n, int K, const HeadArgs& h, hipStream_t st) {
     if (K % 32 || n <= 0 || n > 128 || V <= 0) throw ArgError(-1, "head_argmax: unsupported shape");
-    const int nks = K / 32, tiles = (V + 31) / 32;
-    WMI_SKINNY_NT(n, WMI_SKINNY_U(K, NT, hipLaunchKernelGGL((head_argmax_kernel<NT, U>), dim3(tiles), dim3(256), 0,
-                                                             st, W, X, nks, n, K, h)));
+    const int nks = K / KSTEP<T>, tiles = (V + 31) / 32;
+    WMI_SKINNY_NT(n, WMI_SKINNY_U(nks, NT, hipLaunchKernelGGL((head_argmax_kernel<T, NT, U>), dim3(tiles), dim3(256), 0,
+                                                              st, W, X, nks, n, K, h)));
     return tiles;
 }
 
