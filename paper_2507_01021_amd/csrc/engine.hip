@@ -264,16 +264,6 @@ class EngineT final : public Engine {
         prefill_ = !ctc_ && p.prefill != 0;
         WMI_HIP(hipSetDevice(dev_));
         WMI_HIP(hipStreamCreateWithFlags(&own_stream_, hipStreamNonBlocking));
-        for (int c = 1; c < MAXC; ++c) {
-            WMI_HIP(hipStreamCreateWithFlags(&cst_[c], hipStreamNonBlocking));
-            WMI_HIP(hipEventCreateWithFlags(&join_ev_[c], hipEventDisableTiming));
-        }
-        WMI_HIP(hipEventCreateWithFlags(&fork_ev_, hipEventDisableTiming));
-        for (int k = 0; k < ENC_PARTS_MAX - 1; ++k) {
-            WMI_HIP(hipStreamCreateWithFlags(&es_[k], hipStreamNonBlocking));
-            WMI_HIP(hipEventCreateWithFlags(&enc_join_[k], hipEventDisableTiming));
-        }
-        WMI_HIP(hipEventCreateWithFlags(&enc_fork_, hipEventDisableTiming));
         st_ = own_stream_;
         if (const char* g = getenv("WHISPER_STEP_GRAPHS")) graphs_ = g[0] != '0';
         if (const char* g = getenv("WHISPER_STEP_SPLIT")) split_ = g[0] != '0';
@@ -281,7 +271,20 @@ class EngineT final : public Engine {
         if (const char* g = getenv("WHISPER_FUSED_LN")) fused_ln_ = g[0] != '0';
         if (const char* g = getenv("WHISPER_FREE_CHAINS")) free_run_ = g[0] != '0';
         if (const char* g = getenv("WHISPER_FC2_SPLIT")) fc2_split_ = atoi(g);
-        if (const char* g = getenv("WHISPER_ENC_SPLIT")) enc_parts_ = std::max(1, std::min(ENC_PARTS_MAX, atoi(g)));
+        if (const char* g = getenv("WHISPER_ENC_SPLIT")) enc_parts_ = std::max(1, std::min(MAXC, atoi(g)));
+        // Side streams, created right after the context's own and no more
+        // than are used: a process has four hardware queues, which streams
+        // take in turn, and two streams on one queue do not overlap. (With
+        // seven streams per context, whether the two halves of a pass
+        // overlapped depended on the contexts created before: 5 turbo
+        // segments took 17.5 or 28.1 ms.) The decode chains and the parts of
+        // an encoder pass are never in flight together and share them.
+        if (std::is_same<T, bf16>::value)
+            for (int c = 1; c < std::max(ctc_ ? 1 : chains_, enc_parts_); ++c) {
+                WMI_HIP(hipStreamCreateWithFlags(&cst_[c], hipStreamNonBlocking));
+                WMI_HIP(hipEventCreateWithFlags(&join_ev_[c], hipEventDisableTiming));
+            }
+        WMI_HIP(hipEventCreateWithFlags(&fork_ev_, hipEventDisableTiming));
         load_weights(blob, bytes);
         alloc_state();
         scratch_ = static_cast<unsigned char*>(scratch_address(dev_));
@@ -291,8 +294,6 @@ class EngineT final : public Engine {
     ~EngineT() override {
         (void)hipSetDevice(dev_);
         if (st_) (void)hipStreamSynchronize(st_);
-        for (auto q : es_)
-            if (q) (void)hipStreamSynchronize(q);
         if (ctc_st_) (void)hipStreamSynchronize(ctc_st_);
         for (auto& pr : prof_)
             for (auto& e : pr.used) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
@@ -325,11 +326,6 @@ class EngineT final : public Engine {
             if (ctc_done_[q]) (void)hipEventDestroy(ctc_done_[q]);
         }
         if (ctc_st_) (void)hipStreamDestroy(ctc_st_);
-        if (enc_fork_) (void)hipEventDestroy(enc_fork_);
-        for (int k = 0; k < ENC_PARTS_MAX - 1; ++k) {
-            if (enc_join_[k]) (void)hipEventDestroy(enc_join_[k]);
-            if (es_[k]) (void)hipStreamDestroy(es_[k]);
-        }
         if (own_stream_) (void)hipStreamDestroy(own_stream_);
     }
 
@@ -1014,10 +1010,8 @@ class EngineT final : public Engine {
     bool stamp_on_ = false;                 // launches being made carry cross-attention stamps
     unsigned long long* stamps_ = nullptr;  // [chain][layer][2] stamp slots
     double wall_khz_ = 100000.0;            // real-time counter ticks per millisecond
-    hipStream_t cst_[MAXC] = {};                                   // streams of chains 1.. (chain 0: st_)
-    static constexpr int ENC_PARTS_MAX = 4;
-    hipStream_t es_[ENC_PARTS_MAX - 1] = {};                       // the encoder pass's parts 1..
-    hipEvent_t enc_fork_ = nullptr, enc_join_[ENC_PARTS_MAX - 1] = {};
+    // side streams: decode chains 1.. and parts 1.. of an encoder pass (chain and part 0: st_)
+    hipStream_t cst_[MAXC] = {};
     int enc_parts_ = 2;
     hipEvent_t fork_ev_ = nullptr, join_ev_[MAXC] = {};
     // host staging
@@ -1245,16 +1239,16 @@ class EngineT final : public Engine {
                               ? std::min(enc_parts_, nb)
                               : 1;
         if (parts > 1) {
-            WMI_HIP(hipEventRecord(enc_fork_, st_));
-            for (int k = 1; k < parts; ++k) WMI_HIP(hipStreamWaitEvent(es_[k - 1], enc_fork_, 0));
+            WMI_HIP(hipEventRecord(fork_ev_, st_));
+            for (int k = 1; k < parts; ++k) WMI_HIP(hipStreamWaitEvent(cst_[k], fork_ev_, 0));
             for (int l = 0; l < Le_; ++l)
                 for (int k = 0; k < parts; ++k) {
                     const int b0 = nb * k / parts, b1 = nb * (k + 1) / parts;
-                    encoder_layer(l, b0, b1 - b0, k == 0 ? st_ : es_[k - 1]);
+                    encoder_layer(l, b0, b1 - b0, k == 0 ? st_ : cst_[k]);
                 }
             for (int k = 1; k < parts; ++k) {
-                WMI_HIP(hipEventRecord(enc_join_[k - 1], es_[k - 1]));
-                WMI_HIP(hipStreamWaitEvent(st_, enc_join_[k - 1], 0));
+                WMI_HIP(hipEventRecord(join_ev_[k], cst_[k]));
+                WMI_HIP(hipStreamWaitEvent(st_, join_ev_[k], 0));
             }
         } else {
             for (int l = 0; l < Le_; ++l) encoder_layer(l, 0, nb, st_);
