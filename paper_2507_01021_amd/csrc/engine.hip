@@ -479,10 +479,14 @@ class EngineT final : public Engine {
         int* rowlen;
         float* pbuf;
         unsigned long long* stamps = nullptr;  // cross-attention timing slots [layer][2], or null
+        // prefill rows: groups of up to XR consecutive rows of one slot (ngroups + 1 first rows)
+        const int* groups = nullptr;
+        int ngroups = 0;
     };
 
     // Embedding and every decoder layer for n rows; leaves the final layer
-    // norm of each row in b.dz.
+    // norm of each row in b.dz. Prefill rows only fill the self-attention
+    // caches: they end once the last layer's keys and values are appended.
     void decoder_layers(const RowBufs& b, int n, hipStream_t s) {
         const int d = d_;
         const int ks1 = split_k(d);
@@ -496,6 +500,7 @@ class EngineT final : public Engine {
                  EpiDecQKV<T>{L.bq, L.bv, b.dq, kts_ + sl * TS, vs_ + sl * TS, b.list, pos_, b.rowpos, b.rowlen, d,
                               H_},
                  s);
+            if (b.groups && l + 1 == Ld_) return;
             DecAttnArgs sa{b.dq, kts_ + sl * TS, vs_ + sl * TS, b.datt, b.list, b.rowlen, TS, H_, d};
             prof_begin(WHISPER_K_SELF_ATTN, s);
             if constexpr (std::is_same<T, bf16>::value)
@@ -507,7 +512,10 @@ class EngineT final : public Engine {
             DecAttnArgs ca{b.dq, ktc_ + sl * TC, vc_ + sl * TC, b.datt, b.list, nullptr, TC, H_, d,
                            b.stamps ? b.stamps + 2 * l : nullptr};
             prof_begin(WHISPER_K_CROSS_ATTN, s);
-            hipLaunchKernelGGL(cross_attn_kernel<T>, dim3(H_, n), dim3(64 * CW), 0, s, ca);
+            if (b.groups)
+                hipLaunchKernelGGL(cross_attn_rows_kernel<T>, dim3(H_, b.ngroups), dim3(64 * CW), 0, s, ca, b.groups);
+            else
+                hipLaunchKernelGGL(cross_attn_kernel<T>, dim3(H_, n), dim3(64 * CW), 0, s, ca);
             prof_end(WHISPER_K_CROSS_ATTN, s);
             proj_resid(L.Wco, b.datt, n, d, ks1, L.cbo, L.ln3g, L.ln3b, b.pbuf, b.dx, b.dz, s);
             proj(L.W1, 4 * d, b.dz, n, d, 1, EpiGelu<T, true>{L.b1, b.dh, 4 * d}, s);
@@ -647,27 +655,28 @@ class EngineT final : public Engine {
     // Prompt prefill of one encoder pass (prefill_ on): every seated slot's
     // positions 0 .. n_prompt - 2 run through the decoder layers as rows of
     // their own (no output head), writing the self-attention caches. Rows
-    // are ordered by position, so a chunk of PF_ROWS rows never needs a
-    // position of a later chunk; within a chunk, each layer appends all keys
+    // are ordered by slot, then position, so a slot's positions never need
+    // those of a later chunk; within a chunk, each layer appends all keys
     // and values before its attention reads them.
     void prefill_pass(const SegmentDesc* segs, int nb, const int* slots) {
-        std::vector<int> rows;  // PF list block, then the position block
-        int maxp = 0;
-        for (int i = 0; i < nb; ++i) maxp = std::max(maxp, segs[i].n_prompt - 1);
-        std::vector<int> rl, rp;
-        for (int p = 0; p < maxp; ++p)
-            for (int i = 0; i < nb; ++i)
-                if (p < segs[i].n_prompt - 1) { rl.push_back(slots[i]); rp.push_back(p); }
+        std::vector<int> rl, rp;  // slot and position of every row
+        for (int i = 0; i < nb; ++i)
+            for (int p = 0; p + 1 < segs[i].n_prompt; ++p) { rl.push_back(slots[i]); rp.push_back(p); }
         const int R = (int)rl.size();
-        if (R == 0) return;
-        rows.resize(2 * (size_t)pf_cap_);
+        std::vector<int> up(3 * (size_t)pf_cap_ + 1);  // slots | positions | group starts
         for (int c0 = 0; c0 < R; c0 += pf_cap_) {
             const int n = std::min(pf_cap_, R - c0);
-            std::copy(rl.begin() + c0, rl.begin() + c0 + n, rows.begin());
-            std::copy(rp.begin() + c0, rp.begin() + c0 + n, rows.begin() + pf_cap_);
-            upload(3, pf_list_, rows.data(), rows.size() * sizeof(int));
-            const RowBufs b{pf_list_, pf_list_ + pf_cap_, pf_dx_, pf_dz_, pf_dq_, pf_datt_, pf_dh_, pf_rowlen_,
-                            pf_part_};
+            std::copy(rl.begin() + c0, rl.begin() + c0 + n, up.begin());
+            std::copy(rp.begin() + c0, rp.begin() + c0 + n, up.begin() + pf_cap_);
+            int* gs = up.data() + 2 * (size_t)pf_cap_;
+            int ng = 0;
+            for (int r = 0; r < n; ++r)
+                if (r == 0 || up[r] != up[r - 1] || r - gs[ng - 1] == XR) gs[ng++] = r;
+            gs[ng] = n;
+            upload(3, pf_list_, up.data(), up.size() * sizeof(int));
+            RowBufs b{pf_list_, pf_list_ + pf_cap_, pf_dx_, pf_dz_, pf_dq_, pf_datt_, pf_dh_, pf_rowlen_, pf_part_};
+            b.groups = pf_list_ + 2 * (size_t)pf_cap_;
+            b.ngroups = ng;
             decoder_layers(b, n, st_);
         }
     }
@@ -982,8 +991,8 @@ class EngineT final : public Engine {
     static constexpr int KSMAX = 8;  // most split-K partials of a decode projection
     int fc2_split_ = 8;  // split-K of fc2 (K = 4d) where 4d / 32 is a multiple of 8
     int apart_nc_ = 0;
-    // prompt prefill: rows per chunk (the skinny projections take up to 128)
-    // and the chunk's buffers; the list block is followed by the positions
+    // prompt prefill: rows per chunk and the chunk's buffers; the list block
+    // is followed by the positions and the groups' first rows
     bool prefill_ = false;
     int pf_cap_ = 0;
     int *pf_list_ = nullptr, *pf_rowlen_ = nullptr;
@@ -1475,8 +1484,10 @@ class EngineT final : public Engine {
         keys_ = dalloc<unsigned long long>(S * (size_t)nkeys_);
         dec_err_ = dalloc<int>(1);
         if (prefill_) {
-            pf_cap_ = 128;
-            pf_list_ = dalloc<int>(2 * pf_cap_);
+            // 2048 rows give every projection two or more workgroups per CU
+            // (0.13 GB at d = 1280); no more than a pass can have
+            pf_cap_ = std::min<int>(2048, ((int)EB * 447 + 15) / 16 * 16);
+            pf_list_ = dalloc<int>(3 * (size_t)pf_cap_ + 1);
             pf_rowlen_ = dalloc<int>(pf_cap_);
             pf_dx_ = dalloc<float>((size_t)pf_cap_ * d);
             pf_dz_ = dalloc<T>((size_t)pf_cap_ * d);

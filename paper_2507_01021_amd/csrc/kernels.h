@@ -1120,6 +1120,157 @@ __global__ __launch_bounds__(64 * CW) void cross_attn_kernel(DecAttnArgs a) {
     }
 }
 
+// Prefill: the same cross-attention for up to XR rows of one slot per
+// workgroup, so that the slot's keys and values are read once for all of
+// them (one row at a time, 223 prompt positions read 384 KB per head 223
+// times). Every result is computed with cross_attn_kernel's operations in
+// its order, so a prefilled position equals a stepped one bit for bit; a
+// row's query sits one dim per lane and is broadcast by readlane. With 8
+// rows the kernel is bound by its fp32 FMAs, not by the caches' bytes: 3568
+// rows x 12 heads take 0.66 ms per layer, one row per workgroup 2.04 ms.
+constexpr int XR = 8;
+
+template <class T> struct Packed;  // loads kept in their storage type until used
+template <> struct Packed<bf16> {
+    static constexpr int W = 2;
+    static __device__ __forceinline__ void ld(const bf16* p, uint32_t* w, int n) {
+        for (int i = 0; i < n; i += 4) {
+            const u32x2 u = *reinterpret_cast<const u32x2*>(p + i);
+            w[i / 2] = u.x;
+            w[i / 2 + 1] = u.y;
+        }
+    }
+    static __device__ __forceinline__ float at(const uint32_t* w, int i) {
+        return __uint_as_float(i & 1 ? w[i / 2] & 0xffff0000u : w[i / 2] << 16);
+    }
+};
+template <> struct Packed<float> {
+    static constexpr int W = 1;
+    static __device__ __forceinline__ void ld(const float* p, uint32_t* w, int n) {
+        for (int i = 0; i < n; i += 4) {
+            const u32x4 u = *reinterpret_cast<const u32x4*>(p + i);
+            w[i] = u.x; w[i + 1] = u.y; w[i + 2] = u.z; w[i + 3] = u.w;
+        }
+    }
+    static __device__ __forceinline__ float at(const uint32_t* w, int i) { return __uint_as_float(w[i]); }
+};
+
+// groups[g] = first row of group g; groups[g + 1] - groups[g] <= XR rows of one slot
+template <class T>
+__global__ __launch_bounds__(64 * CW) void cross_attn_rows_kernel(DecAttnArgs a, const int* __restrict__ groups) {
+    typedef Packed<T> P;
+    __shared__ float ps[CW][XR][256];
+    __shared__ float ml[CW][XR][2];
+    __shared__ float op[CW][XR][64];
+    const int h = blockIdx.x, r0 = groups[blockIdx.y], nr = groups[blockIdx.y + 1] - r0;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const long long head = (long long)a.list[r0] * a.H + h;
+    const T* kt = reinterpret_cast<const T*>(a.kt) + head * 64 * a.TP;
+    const T* vv = reinterpret_cast<const T*>(a.v) + head * a.TP * 64;
+    const int start = 256 * w, p0 = start + lane * 4;
+    float qv[XR], s[XR][4];
+#pragma unroll
+    for (int r = 0; r < XR; ++r) {
+        qv[r] = ldf(reinterpret_cast<const T*>(a.q) + (long long)(r0 + min(r, nr - 1)) * a.d + h * 64 + lane);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[r][i] = 0.f;
+    }
+    const int pk = min(p0, a.TP - 4);  // the last wave's lanes beyond the window read padding
+#pragma unroll 1
+    for (int j0 = 0; j0 < 64; j0 += 8) {
+        uint32_t kv[8][4 / P::W];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) P::ld(kt + (long long)(j0 + j) * a.TP + pk, kv[j], 4);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            float k4[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) k4[i] = P::at(kv[j], i);
+#pragma unroll
+            for (int r = 0; r < XR; ++r) {
+                const float qj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(qv[r]), j0 + j));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[r][i] = fmaf(qj, k4[i], s[r][i]);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < XR; ++r) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[r][i] = (p0 + i < N_CTX) ? s[r][i] * LOG2E : -INFINITY;
+            mx = fmaxf(mx, s[r][i]);
+        }
+        mx = wave_max(mx);
+        float lsum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float p = (p0 + i < N_CTX) ? exp2_softmax(s[r][i] - mx) : 0.f;
+            ps[w][r][lane * 4 + i] = p;
+            lsum += p;
+        }
+        lsum = wave_sum(lsum);
+        if (lane == 0) { ml[w][r][0] = mx; ml[w][r][1] = lsum; }
+    }
+    __syncthreads();
+    const int dg = lane & 7, pg = lane >> 3;
+    float o[XR][8];
+#pragma unroll
+    for (int r = 0; r < XR; ++r)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[r][i] = 0.f;
+    const int nloc = min(256, N_CTX - start);
+#pragma unroll 1
+    for (int b0 = 0; b0 < 256; b0 += 32) {
+        uint32_t vr[4][8 / P::W];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            P::ld(vv + (long long)(start + min(b0 + pg + 8 * u, nloc - 1)) * 64 + dg * 8, vr[u], 8);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int pp = b0 + pg + 8 * u, pc = min(pp, nloc - 1);
+            float v8[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v8[i] = P::at(vr[u], i);
+#pragma unroll
+            for (int r = 0; r < XR; ++r) {
+                const float pw = pp < nloc ? ps[w][r][pc] : 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) o[r][i] = fmaf(pw, v8[i], o[r][i]);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < XR; ++r) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            o[r][i] += __shfl_xor(o[r][i], 8, 64);
+            o[r][i] += __shfl_xor(o[r][i], 16, 64);
+            o[r][i] += __shfl_xor(o[r][i], 32, 64);
+        }
+        if (lane < 8) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) op[w][r][dg * 8 + i] = o[r][i];
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < nr * 64; e += 64 * CW) {
+        const int r = e >> 6, c = e & 63;
+        float M = ml[0][r][0];
+#pragma unroll
+        for (int k = 1; k < CW; ++k) M = fmaxf(M, ml[k][r][0]);
+        float L = 0.f, acc = 0.f;
+#pragma unroll
+        for (int k = 0; k < CW; ++k) {
+            const float wgt = exp2_softmax(ml[k][r][0] - M);
+            L += wgt * ml[k][r][1];
+            acc += wgt * op[k][r][c];
+        }
+        stf(reinterpret_cast<T*>(a.out) + dec_off<T>(r0 + r, h * 64 + c, a.d), acc / L);
+    }
+}
+
 // Timing slots of n launches: start = all ones (for a minimum), end = 0.
 __global__ void stamp_reset_kernel(unsigned long long* __restrict__ s, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1140,7 +1291,8 @@ __global__ void stamp_reset_kernel(unsigned long long* __restrict__ s, int n) {
 // take interleaved k-steps, U steps' loads issued before their
 // MFMAs; the wave partial sums are added in LDS in a fixed order, so a row's
 // result never depends on which other rows are present (row tiles past n
-// re-read the last valid tile and are dropped). The fp32 model's projections
+// re-read the last valid tile and are dropped). Rows beyond 16 * NT go to
+// further workgroups (grid z). The fp32 model's projections
 // took 37 us each (d = 384, 7 rows) as a GEMM of 64 x 64 vector-FMA tiles and
 // 12 us on its MFMA tiles; here 3.4-3.8 us, a launch's latency. NW waves per workgroup
 // (4, or more for long reductions), red: (NW - 1) * RT * NT * 4 * 64 floats.
@@ -1237,25 +1389,25 @@ __global__ __launch_bounds__(64 * NW) void skinny_kernel(const T* __restrict__ W
     __shared__ float red[(NW - 1) * RT * NT * 4 * 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int fr = lane & 15, fc = lane >> 4;
-    const int i0 = blockIdx.x * 16 * RT;
+    const int i0 = blockIdx.x * 16 * RT, r0 = blockIdx.z * 16 * NT;
     EpiPre pre[RT][NT];
     if (wave == 0) {
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
             for (int u = 0; u < NT; ++u) {
-                const int i = i0 + t * 16 + fc * 4, r = u * 16 + fr;
+                const int i = i0 + t * 16 + fc * 4, r = r0 + u * 16 + fr;
                 if (i < MA && r < n) pre[t][u] = epi.pre(i, r, blockIdx.y);
             }
     }
     float v[RT][NT][4];
-    skinny_core<T, RT, NT, U, NW>(W, X, nks_tot, n, Kc, red, v);
+    skinny_core<T, RT, NT, U, NW>(W, X + (long long)r0 * nks_tot * KSTEP<T>, nks_tot, min(n - r0, 16 * NT), Kc, red, v);
     if (wave > 0) return;
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
-            const int i = i0 + t * 16 + fc * 4, r = u * 16 + fr;
+            const int i = i0 + t * 16 + fc * 4, r = r0 + u * 16 + fr;
             if (i < MA && r < n) epi(i, r, blockIdx.y, v[t][u][0], v[t][u][1], v[t][u][2], v[t][u][3], pre[t][u]);
         }
 }
@@ -1435,81 +1587,151 @@ __global__ __launch_bounds__(64 * sln::NW) void skinny_ln_kernel(const bf16* __r
 }
 
 // U = k-steps per wave and batch for nks k-steps over 4 waves: all of a
-// wave's steps in one batch, up to 10 (4 with 8 row tiles, for registers).
-constexpr int skinny_u(int nks, int NT) {
+// wave's steps in one batch, up to 10.
+constexpr int skinny_u(int nks) {
     return (nks + 3) / 4 <= 1 ? 1
          : (nks + 3) / 4 <= 2 ? 2
          : (nks + 3) / 4 <= 3 ? 3
-         : ((nks + 3) / 4 <= 4 || NT >= 8) ? 4
+         : (nks + 3) / 4 <= 4 ? 4
          : (nks + 3) / 4 <= 6 ? 6 : 10;
 }
 
-#define WMI_SKINNY_U(nks, NT, LAUNCH)                                                 \
+#define WMI_SKINNY_U(nks, LAUNCH)                                                     \
     do {                                                                             \
-        const int u_ = skinny_u(nks, NT);                                             \
+        const int u_ = skinny_u(nks);                                                 \
         if (u_ == 1) { constexpr int U = 1; LAUNCH; }                                 \
         else if (u_ == 2) { constexpr int U = 2; LAUNCH; }                            \
         else if (u_ == 3) { constexpr int U = 3; LAUNCH; }                            \
         else if (u_ == 4) { constexpr int U = 4; LAUNCH; }                            \
-        else if (u_ == 6) { constexpr int U = (NT) >= 8 ? 4 : 6; LAUNCH; }             \
-        else { constexpr int U = (NT) >= 8 ? 4 : 10; LAUNCH; }                        \
+        else if (u_ == 6) { constexpr int U = 6; LAUNCH; }                            \
+        else { constexpr int U = 10; LAUNCH; }                                        \
     } while (0)
 
+// Row tiles per workgroup; more than 64 rows take several groups of 64.
 #define WMI_SKINNY_NT(n, ...)                                         \
     do {                                                             \
         if ((n) <= 16) { constexpr int NT = 1; __VA_ARGS__; }          \
         else if ((n) <= 32) { constexpr int NT = 2; __VA_ARGS__; }     \
-        else if ((n) <= 64) { constexpr int NT = 4; __VA_ARGS__; }     \
-        else { constexpr int NT = 8; __VA_ARGS__; }                    \
+        else { constexpr int NT = 4; __VA_ARGS__; }                    \
     } while (0)
+
+// Many rows (prompt prefill): the same projection with the waves' split over
+// output tiles instead of the reduction. A wave owns 32 weight rows x 64
+// activation rows and runs the NW interleaved k-step sequences of
+// skinny_core's NW waves one after another, adding each sequence's sum to the
+// total in their order, so that a result is the same bit for bit while every
+// loaded fragment feeds two or four MFMAs and every wave has an epilogue of
+// its own. Bound by the L1's 64 bytes per clock (24 KB of fragments per
+// k-step and workgroup against 128 MFMA cycles). 3568 rows, d = 768: a
+// layer's two split-K projections take 86 us, as 28 chunks of 128 rows in
+// skinny_kernel 377 us.
+template <class T, int NW, class Epi>
+__global__ __launch_bounds__(256) void many_kernel(const T* __restrict__ W, const T* __restrict__ X, int nks_tot, int n,
+                                                   int Kc, Epi epi) {
+    typedef typename Frag<T>::type frag;
+    constexpr int RT = 2, NT = 4, U = 3, EL = 16 / sizeof(T);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int fr = lane & 15, fc = lane >> 4;
+    const int tile = (blockIdx.x * 4 + wave) * RT, r0 = blockIdx.z * 64;
+    const int nks = Kc / KSTEP<T>, s_base = blockIdx.y * nks, ulast = (n - 1) >> 4;
+    const T* wp[RT];
+    const T* xp[NT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) wp[t] = W + (((long long)(tile + t) * nks_tot + s_base) * 64 + lane) * EL;
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+        xp[u] = X + (((long long)min((r0 >> 4) + u, ulast) * nks_tot + s_base) * 64 + lane) * EL;
+    mfma_f32x4 tot[RT][NT];
+#pragma unroll 1
+    for (int w = 0; w < NW; ++w) {
+        mfma_f32x4 acc[RT][NT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) acc[t][u] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int s0 = w; s0 < nks; s0 += NW * U) {
+            frag a[U][RT], b[U][NT];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int off = min(s0 + NW * q, nks - 1) * 64 * EL;
+#pragma unroll
+                for (int t = 0; t < RT; ++t) a[q][t] = *reinterpret_cast<const frag*>(wp[t] + off);
+#pragma unroll
+                for (int u = 0; u < NT; ++u) b[q][u] = *reinterpret_cast<const frag*>(xp[u] + off);
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                if (s0 + NW * q < nks) {
+#pragma unroll
+                    for (int t = 0; t < RT; ++t)
+#pragma unroll
+                        for (int u = 0; u < NT; ++u) acc[t][u] = Frag<T>::mma(a[q][t], b[q][u], acc[t][u]);
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int u = 0; u < NT; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tot[t][u][e] = w == 0 ? acc[t][u][e] : tot[t][u][e] + acc[t][u][e];
+    }
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+        const int r = r0 + u * 16 + fr;
+        if (r >= n) continue;
+        EpiPre pre[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) pre[t] = epi.pre((tile + t) * 16 + fc * 4, r, blockIdx.y);
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+            epi((tile + t) * 16 + fc * 4, r, blockIdx.y, tot[t][u][0], tot[t][u][1], tot[t][u][2], tot[t][u][3], pre[t]);
+    }
+}
+// Worth it once its workgroups (128 weight rows x 64 rows) reach half the
+// CUs; below that the one-tile workgroups spread better.
+inline bool many_rows(int MA, int KS, int groups) { return MA % 128 == 0 && MA / 128 * KS * groups >= 128; }
 
 // Waves per workgroup of a residual projection (whole reduction in one
 // workgroup): twice the usual, to keep more loads in flight. The same for
 // every row count, since the waves' k-step split fixes the summation order.
 constexpr int RESID_NW = 8;
-// k-steps per wave and batch for nks k-steps over NW waves (fewer with many
-// row tiles, for registers)
-constexpr int resid_u(int nks, int NW, int NT) {
+// k-steps per wave and batch for nks k-steps over NW waves
+constexpr int resid_u(int nks, int NW) {
     return (nks + NW - 1) / NW <= 1 ? 1
-         : ((nks + NW - 1) / NW <= 2 || NT >= 8) ? 2
+         : (nks + NW - 1) / NW <= 2 ? 2
          : (nks + NW - 1) / NW <= 3 ? 3
          : (nks + NW - 1) / NW <= 4 ? 4
          : (nks + NW - 1) / NW <= 6 ? 6 : 10;
 }
 #define WMI_RESID_U(nks, NW, NT, LAUNCH)                                              \
     do {                                                                             \
-        const int u_ = resid_u(nks, NW, NT);                                          \
+        const int u_ = resid_u(nks, NW);                                              \
         if (u_ == 1) { constexpr int U = 1; LAUNCH; }                                 \
         else if (u_ == 2) { constexpr int U = 2; LAUNCH; }                            \
-        else if (u_ == 3) { constexpr int U = (NT) >= 8 ? 2 : 3; LAUNCH; }             \
-        else if (u_ == 4) { constexpr int U = (NT) >= 8 ? 2 : 4; LAUNCH; }             \
-        else if (u_ == 6) { constexpr int U = (NT) >= 8 ? 2 : 6; LAUNCH; }             \
-        else { constexpr int U = (NT) >= 8 ? 2 : (NT) >= 4 ? 6 : 10; LAUNCH; }        \
+        else if (u_ == 3) { constexpr int U = 3; LAUNCH; }                            \
+        else if (u_ == 4) { constexpr int U = 4; LAUNCH; }                            \
+        else if (u_ == 6) { constexpr int U = 6; LAUNCH; }                            \
+        else { constexpr int U = (NT) >= 4 ? 6 : 10; LAUNCH; }                        \
     } while (0)
 
 // x[r] += W X[r] + bias for n rows (W fragment-major [d rounded up to 32][K],
 // X fragment-major [n rounded up to 16][K], x row-major fp32 [n][d]).
-// More than 64 rows go in launches of 64 (a row's result does not depend on
-// the other rows of its launch).
 inline void skinny_resid(const bf16* W, int d, const bf16* X, int n, int K, const float* bias, float* x,
                          hipStream_t st) {
-    if (K % 32 || n <= 0 || n > 128 || d % 16) throw ArgError(-1, "skinny_resid: unsupported shape");
-    const int nks = K / 32;
-    const dim3 grid(d / 16, 1);
-    for (int r0 = 0; r0 < n; r0 += 64) {
-        const int m = min(64, n - r0);
-        const bf16* Xr = X + (size_t)r0 * K;
-        const EpiResidX epi{bias, x + (size_t)r0 * d, d};
-        auto launch = [&](auto nt) {
-            constexpr int NT = decltype(nt)::value;
-            WMI_RESID_U(nks, RESID_NW, NT,
-                        hipLaunchKernelGGL((skinny_kernel<bf16, 1, NT, U, EpiResidX, RESID_NW>), grid,
-                                           dim3(64 * RESID_NW), 0, st, W, Xr, nks, d, m, K, epi));
-        };
-        if (m <= 16) launch(std::integral_constant<int, 1>{});
-        else if (m <= 32) launch(std::integral_constant<int, 2>{});
-        else launch(std::integral_constant<int, 4>{});
+    if (K % 32 || n <= 0 || d % 32) throw ArgError(-1, "skinny_resid: unsupported shape");
+    const int nks = K / 32, groups = (n + 63) / 64;
+    const EpiResidX epi{bias, x, d};
+    if (many_rows(d, 1, groups)) {
+        hipLaunchKernelGGL((many_kernel<bf16, RESID_NW, EpiResidX>), dim3(d / 128, 1, groups), dim3(256), 0, st, W, X, nks,
+                           n, K, epi);
+        return;
     }
+    WMI_SKINNY_NT(n, WMI_RESID_U(nks, RESID_NW, NT,
+                                 hipLaunchKernelGGL((skinny_kernel<bf16, 1, NT, U, EpiResidX, RESID_NW>),
+                                                    dim3(d / 16, 1, groups), dim3(64 * RESID_NW), 0, st, W, X, nks, d, n,
+                                                    K, epi)));
 }
 
 // C = W LN(x) for n rows of the fp32 residual stream x (row-major, width d),
@@ -1520,8 +1742,15 @@ inline void skinny_resid(const bf16* W, int d, const bf16* X, int n, int K, cons
 template <class Epi>
 inline void skinny_ln(const bf16* W, int MA, const float* x, int n, int d, const float* g, const float* b,
                       const Epi& epi, hipStream_t st) {
-    if (n <= 0 || n > 128 || MA <= 0 || MA % 16) throw ArgError(-1, "skinny_ln: unsupported shape");
+    if (n <= 0 || MA <= 0 || MA % 16) throw ArgError(-1, "skinny_ln: unsupported shape");
     const int groups = (n + 15) / 16;
+    if (MA % 32 == 0 && MA / 32 * groups >= 512) {
+        // many rows (prompt prefill): half as many workgroups repeat a row's
+        // normalisation, still two per CU
+        WMI_SWITCH_E(d, hipLaunchKernelGGL((skinny_ln_kernel<2, E, Epi>), dim3(MA / 32, groups), dim3(64 * sln::NW), 0,
+                                           st, W, x, g, b, MA, n, epi));
+        return;
+    }
     WMI_SWITCH_E(d, hipLaunchKernelGGL((skinny_ln_kernel<1, E, Epi>), dim3(MA / 16, groups), dim3(64 * sln::NW), 0,
                                        st, W, x, g, b, MA, n, epi));
 }
@@ -1530,11 +1759,16 @@ inline void skinny_ln(const bf16* W, int MA, const float* x, int n, int d, const
 // to 16][K]; KS workgroups split K.
 template <class T, class Epi>
 inline void skinny(const T* W, int MA, const T* X, int n, int K, int KS, const Epi& epi, hipStream_t st) {
-    if (KS < 1 || K % (KSTEP<T> * KS) || n <= 0 || n > 128 || MA <= 0) throw ArgError(-1, "skinny: unsupported shape");
-    const int Kc = K / KS, nks_tot = K / KSTEP<T>;
-    const dim3 grid((MA + 15) / 16, KS);
-    WMI_SKINNY_NT(n, WMI_SKINNY_U(Kc / KSTEP<T>, NT, hipLaunchKernelGGL((skinny_kernel<T, 1, NT, U, Epi>), grid,
-                                                                        dim3(256), 0, st, W, X, nks_tot, MA, n, Kc, epi)));
+    if (KS < 1 || K % (KSTEP<T> * KS) || n <= 0 || MA <= 0) throw ArgError(-1, "skinny: unsupported shape");
+    const int Kc = K / KS, nks_tot = K / KSTEP<T>, groups = (n + 63) / 64;
+    if (many_rows(MA, KS, groups)) {
+        hipLaunchKernelGGL((many_kernel<T, 4, Epi>), dim3(MA / 128, KS, groups), dim3(256), 0, st, W, X, nks_tot, n, Kc,
+                           epi);
+        return;
+    }
+    WMI_SKINNY_NT(n, WMI_SKINNY_U(Kc / KSTEP<T>, hipLaunchKernelGGL((skinny_kernel<T, 1, NT, U, Epi>),
+                                                                    dim3((MA + 15) / 16, KS, groups), dim3(256), 0, st,
+                                                                    W, X, nks_tot, MA, n, Kc, epi)));
 }
 
 // ------------------------------------------------------------- CTC greedy decoding
@@ -1957,12 +2191,12 @@ __global__ __launch_bounds__(256) void head_argmax_kernel(const T* __restrict__ 
     __shared__ float red[3 * RT * NT * 4 * 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int fr = lane & 15, fc = lane >> 4;
-    const int i0 = blockIdx.x * 16 * RT;
+    const int i0 = blockIdx.x * 16 * RT, r0 = blockIdx.z * 16 * NT;
     unsigned excl[RT][NT];  // bit q: id i + q is not admissible for this row
     if (wave == 0) {
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
-            const int r = u * 16 + fr;
+            const int r = r0 + u * 16 + fr;
             bool first = false;
             if (h.f.first && r < n) {
                 const int sl = h.f.list[r];
@@ -1981,11 +2215,11 @@ __global__ __launch_bounds__(256) void head_argmax_kernel(const T* __restrict__ 
         }
     }
     float v[RT][NT][4];
-    skinny_core<T, RT, NT, U>(W, X, nks_tot, n, Kc, red, v);
+    skinny_core<T, RT, NT, U>(W, X + (long long)r0 * nks_tot * KSTEP<T>, nks_tot, min(n - r0, 16 * NT), Kc, red, v);
     if (wave > 0) return;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-        const int r = u * 16 + fr;
+        const int r = r0 + u * 16 + fr;
         unsigned long long k = 0;
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
@@ -2018,10 +2252,10 @@ __global__ __launch_bounds__(256) void head_argmax_kernel(const T* __restrict__ 
 // of keys per row.
 template <class T>
 inline int head_argmax(const T* W, int V, const T* X, int n, int K, const HeadArgs& h, hipStream_t st) {
-    if (K % 32 || n <= 0 || n > 128 || V <= 0) throw ArgError(-1, "head_argmax: unsupported shape");
+    if (K % 32 || n <= 0 || V <= 0) throw ArgError(-1, "head_argmax: unsupported shape");
     const int nks = K / KSTEP<T>, tiles = (V + 31) / 32;
-    WMI_SKINNY_NT(n, WMI_SKINNY_U(nks, NT, hipLaunchKernelGGL((head_argmax_kernel<T, NT, U>), dim3(tiles), dim3(256), 0,
-                                                              st, W, X, nks, n, K, h)));
+    WMI_SKINNY_NT(n, WMI_SKINNY_U(nks, hipLaunchKernelGGL((head_argmax_kernel<T, NT, U>), dim3(tiles, 1, (n + 63) / 64),
+                                                          dim3(256), 0, st, W, X, nks, n, K, h)));
     return tiles;
 }
 
