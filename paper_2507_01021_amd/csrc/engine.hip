@@ -232,6 +232,28 @@ __global__ void put_list_kernel(RowList l, int* __restrict__ dst) {
     if ((int)threadIdx.x < l.n) dst[threadIdx.x] = l.slot[threadIdx.x];
 }
 
+// ------------------------------------------------------------------ side streams
+//
+// A process has four hardware queues (HIP's default), which its streams
+// share; two streams on one queue run one after the other. Which queue a
+// stream gets depends on every stream made before it, so whether a side
+// stream really runs beside the context's stream is tried out: a kernel on
+// one stream waits, for at most PROBE_TICKS of the 100 MHz real-time counter,
+// for a flag that a kernel launched after it on the other stream sets.
+constexpr unsigned long long PROBE_TICKS = 200000;  // 2 ms: the host's own delays must fit
+__global__ void probe_wait_kernel(int* flag, int* seen) {
+    const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+    int f = 0;
+    while (!f && __builtin_amdgcn_s_memrealtime() - t0 < PROBE_TICKS) {
+        f = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_sleep(8);
+    }
+    *seen = f;
+}
+__global__ void probe_set_kernel(int* flag, int v) {
+    __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ------------------------------------------------------------------ engine
 
 template <class T> struct HostElem;
@@ -272,19 +294,13 @@ class EngineT final : public Engine {
         if (const char* g = getenv("WHISPER_FREE_CHAINS")) free_run_ = g[0] != '0';
         if (const char* g = getenv("WHISPER_FC2_SPLIT")) fc2_split_ = atoi(g);
         if (const char* g = getenv("WHISPER_ENC_SPLIT")) enc_parts_ = std::max(1, std::min(MAXC, atoi(g)));
-        // Side streams, created right after the context's own and no more
-        // than are used: a process has four hardware queues, which streams
-        // take in turn, and two streams on one queue do not overlap. (With
-        // seven streams per context, whether the two halves of a pass
-        // overlapped depended on the contexts created before: 5 turbo
-        // segments took 17.5 or 28.1 ms.) The decode chains and the parts of
-        // an encoder pass are never in flight together and share them.
-        if (std::is_same<T, bf16>::value)
-            for (int c = 1; c < std::max(ctc_ ? 1 : chains_, enc_parts_); ++c) {
-                WMI_HIP(hipStreamCreateWithFlags(&cst_[c], hipStreamNonBlocking));
-                WMI_HIP(hipEventCreateWithFlags(&join_ev_[c], hipEventDisableTiming));
-            }
+        // The decode chains and the parts of an encoder pass are never in
+        // flight together and share the side streams; fp32 models use none.
+        if (std::is_same<T, bf16>::value) n_side_ = std::max(ctc_ ? 1 : chains_, enc_parts_) - 1;
+        for (int c = 1; c <= n_side_; ++c) WMI_HIP(hipEventCreateWithFlags(&join_ev_[c], hipEventDisableTiming));
         WMI_HIP(hipEventCreateWithFlags(&fork_ev_, hipEventDisableTiming));
+        probe_ = dalloc<int>(2);
+        choose_side_streams();
         load_weights(blob, bytes);
         alloc_state();
         scratch_ = static_cast<unsigned char*>(scratch_address(dev_));
@@ -300,8 +316,7 @@ class EngineT final : public Engine {
         for (auto e : event_pool_) (void)hipEventDestroy(e);
         for (auto e : marks_) (void)hipEventDestroy(e);
         if (mark_start_) (void)hipEventDestroy(mark_start_);
-        for (int c = 1; c < MAXC; ++c)
-            if (cst_[c]) (void)hipStreamSynchronize(cst_[c]);
+        for (auto q : side_pool_) (void)hipStreamSynchronize(q);
         for (auto* m : {&step_graphs_, &stamped_graphs_})
             for (auto& g : *m)
                 for (auto ge : g.second)
@@ -317,10 +332,9 @@ class EngineT final : public Engine {
         }
         for (void* q : allocs_) (void)hipFree(q);
         if (fork_ev_) (void)hipEventDestroy(fork_ev_);
-        for (int c = 1; c < MAXC; ++c) {
+        for (int c = 1; c < MAXC; ++c)
             if (join_ev_[c]) (void)hipEventDestroy(join_ev_[c]);
-            if (cst_[c]) (void)hipStreamDestroy(cst_[c]);
-        }
+        for (auto q : side_pool_) (void)hipStreamDestroy(q);
         for (int q = 0; q < 2; ++q) {
             if (ctc_head_[q]) (void)hipEventDestroy(ctc_head_[q]);
             if (ctc_done_[q]) (void)hipEventDestroy(ctc_done_[q]);
@@ -333,6 +347,54 @@ class EngineT final : public Engine {
         join_chains();
         WMI_HIP(hipStreamSynchronize(st_));
         st_ = s ? static_cast<hipStream_t>(s) : own_stream_;
+        // never waits for the caller's stream: one that is busy or being
+        // captured keeps the side streams as they are
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st_, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+            hipStreamQuery(st_) == hipSuccess)
+            choose_side_streams();
+        (void)hipGetLastError();  // "not ready" is no error here
+    }
+
+    // Whether stream b runs beside stream a (see probe_wait_kernel).
+    bool overlaps(hipStream_t a, hipStream_t b) {
+        int seen = 0;
+        hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, b, probe_, 0);  // also b's first use
+        WMI_HIP(hipStreamSynchronize(b));
+        hipLaunchKernelGGL(probe_wait_kernel, dim3(1), dim3(1), 0, a, probe_, probe_ + 1);
+        hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, b, probe_, 1);
+        WMI_HIP(hipStreamSynchronize(a));
+        WMI_HIP(hipStreamSynchronize(b));
+        WMI_HIP(hipMemcpy(&seen, probe_ + 1, sizeof(int), hipMemcpyDeviceToHost));
+        return seen != 0;
+    }
+
+    // Picks the side streams cst_[1 .. n_side_] for the context's stream: for
+    // each the first of the pool, or a new one, that runs beside it and beside
+    // the ones already picked; one that does not where none does (the work is
+    // the same then, without the overlap). A context's first stream after the
+    // own one shared its queue in one of four processes: 5 turbo segments took
+    // 28.1 instead of 17.1 ms, a small step of 33 rows 1.6 instead of 1.2 ms.
+    void choose_side_streams() {
+        constexpr size_t POOL = 6;  // streams tried at most
+        for (int c = 1; c <= n_side_; ++c) {
+            cst_[c] = nullptr;
+            hipStream_t spare = nullptr;
+            for (size_t i = 0; i < POOL && !cst_[c]; ++i) {
+                if (i == side_pool_.size()) {
+                    hipStream_t q = nullptr;
+                    WMI_HIP(hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
+                    side_pool_.push_back(q);
+                }
+                bool used = false, beside = true;
+                for (int k = 1; k < c; ++k) used = used || cst_[k] == side_pool_[i];
+                if (used) continue;
+                if (!spare) spare = side_pool_[i];
+                for (int k = 0; k < c && beside; ++k) beside = overlaps(k == 0 ? st_ : cst_[k], side_pool_[i]);
+                if (beside) cst_[c] = side_pool_[i];
+            }
+            if (!cst_[c]) cst_[c] = spare;
+        }
     }
 
     void sync() override {
@@ -1021,6 +1083,9 @@ class EngineT final : public Engine {
     double wall_khz_ = 100000.0;            // real-time counter ticks per millisecond
     // side streams: decode chains 1.. and parts 1.. of an encoder pass (chain and part 0: st_)
     hipStream_t cst_[MAXC] = {};
+    int n_side_ = 0;
+    std::vector<hipStream_t> side_pool_;  // every side stream made; cst_ points into it
+    int* probe_ = nullptr;                // flag and answer of overlaps()
     int enc_parts_ = 2;
     hipEvent_t fork_ev_ = nullptr, join_ev_[MAXC] = {};
     // host staging
