@@ -544,7 +544,12 @@ class EngineT final : public Engine {
         // prefill rows: groups of up to XR consecutive rows of one slot (ngroups + 1 first rows)
         const int* groups = nullptr;
         int ngroups = 0;
+        // room for a split cross-attention's chunk results, and the rows it holds
+        float* xpart = nullptr;
+        int xrows = 0;
     };
+    // Rows whose cross-attention is split by chunk.
+    bool cross_split(int n) const { return n <= 16 && n * H_ <= CROSS_SPLIT_MAX<T>; }
 
     // Embedding and every decoder layer for n rows; leaves the final layer
     // norm of each row in b.dz. Prefill rows only fill the self-attention
@@ -574,12 +579,21 @@ class EngineT final : public Engine {
             DecAttnArgs ca{b.dq, ktc_ + sl * TC, vc_ + sl * TC, b.datt, b.list, nullptr, TC, H_, d,
                            b.stamps ? b.stamps + 2 * l : nullptr};
             prof_begin(WHISPER_K_CROSS_ATTN, s);
+            const bool split = n <= b.xrows && cross_split(n);
+            const CrossPart cp{b.xpart, reinterpret_cast<float2*>(b.xpart + (size_t)n * H_ * CW * 64)};
             if (b.groups)
                 hipLaunchKernelGGL(cross_attn_rows_kernel<T>, dim3(H_, b.ngroups), dim3(64 * CW), 0, s, ca, b.groups);
+            else if (split)
+                hipLaunchKernelGGL(cross_attn_split_kernel<T>, dim3(H_, n, CW), dim3(128), 0, s, ca, cp);
             else
                 hipLaunchKernelGGL(cross_attn_kernel<T>, dim3(H_, n), dim3(64 * CW), 0, s, ca);
             prof_end(WHISPER_K_CROSS_ATTN, s);
-            proj_resid(L.Wco, b.datt, n, d, ks1, L.cbo, L.ln3g, L.ln3b, b.pbuf, b.dx, b.dz, s);
+            if (split) {
+                skinny_merge(L.Wco, d, cp, H_, n, d, ks1, EpiPartial{b.pbuf, d, n}, s);
+                resid_ln(ks1, n, L.cbo, L.ln3g, L.ln3b, b.pbuf, b.dx, b.dz, s);
+            } else {
+                proj_resid(L.Wco, b.datt, n, d, ks1, L.cbo, L.ln3g, L.ln3b, b.pbuf, b.dx, b.dz, s);
+            }
             proj(L.W1, 4 * d, b.dz, n, d, 1, EpiGelu<T, true>{L.b1, b.dh, 4 * d}, s);
             const bool last = l + 1 == Ld_;
             proj_resid(L.W2, b.dh, n, 4 * d, ks4, L.b2, last ? lnfg_ : dec_[l + 1].ln1g,
@@ -600,7 +614,8 @@ class EngineT final : public Engine {
         }
         const StepBufs b{RowBufs{list_ + r0, nullptr, dx_ + (size_t)r0 * d, dz_ + (size_t)r0 * d,
                                  dq_ + (size_t)r0 * d, datt_ + (size_t)r0 * d, dh_ + (size_t)r0 * 4 * d,
-                                 rowlen_ + r0, gpart_ + (size_t)c * KSMAX * S_ * d, stamps},
+                                 rowlen_ + r0, gpart_ + (size_t)c * KSMAX * S_ * d, stamps, nullptr, 0,
+                                 c == 0 ? xpart_ : nullptr, c == 0 ? std::min(S_, 16) : 0},
                          logits_ + (size_t)r0 * V_, keys_ + (size_t)r0 * nkeys_, outtok_ + r0,
                          forced ? forced_ + r0 : nullptr};
         run_step(b, n, want_logits, s);
@@ -679,7 +694,10 @@ class EngineT final : public Engine {
         const StepBufs b{RowBufs{list, nullptr, reinterpret_cast<float*>(z + L.dx), reinterpret_cast<T*>(z + L.dz),
                                  reinterpret_cast<T*>(z + L.dq), reinterpret_cast<T*>(z + L.datt),
                                  reinterpret_cast<T*>(z + L.dh), reinterpret_cast<int*>(z + L.rowlen),
-                                 reinterpret_cast<float*>(z + L.part)},
+                                 reinterpret_cast<float*>(z + L.part), nullptr, nullptr, 0,
+                                 // in the MLP's activations, which are written after the merge
+                                 reinterpret_cast<float*>(z + L.dh),
+                                 (int)((L.part - L.dh) / (sizeof(float) * CROSS_PART_FLOATS * H_))},
                          reinterpret_cast<float*>(z + L.logits), reinterpret_cast<unsigned long long*>(z + L.keys),
                          out_tok_dev ? out_tok_dev : reinterpret_cast<int*>(z + L.outtok), nullptr};
         run_step(b, n, false, st_);
@@ -1043,7 +1061,7 @@ class EngineT final : public Engine {
     hipEvent_t stop_ev_[2] = {nullptr, nullptr};
     int64_t snapshots_ = 0;
     T *kts_, *vs_, *ktc_, *vc_, *dz_, *dq_, *datt_, *dh_;
-    float *dx_, *logits_, *gpart_;
+    float *dx_, *logits_, *gpart_, *xpart_;
     unsigned long long* keys_;  // greedy-choice keys [S][nkeys_]
     int nkeys_ = 16;
     int* dec_err_;              // set by a decode step that found no admissible token
@@ -1539,6 +1557,7 @@ class EngineT final : public Engine {
         dh_ = dalloc<T>(S16 * 4 * d);
         logits_ = dalloc<float>(S * (size_t)V_);
         gpart_ = dalloc<float>((size_t)MAXC * KSMAX * S * d);  // split-K partials [chain][KS][rows][d]
+        xpart_ = dalloc<float>(std::min<size_t>(S, 16) * H * CROSS_PART_FLOATS);
         stamps_ = dalloc<unsigned long long>((size_t)MAXC * std::max(Ld_, 1) * 2);
         {
             int khz = 0;

@@ -1120,16 +1120,6 @@ __global__ __launch_bounds__(64 * CW) void cross_attn_kernel(DecAttnArgs a) {
     }
 }
 
-// Prefill: the same cross-attention for up to XR rows of one slot per
-// workgroup, so that the slot's keys and values are read once for all of
-// them (one row at a time, 223 prompt positions read 384 KB per head 223
-// times). Every result is computed with cross_attn_kernel's operations in
-// its order, so a prefilled position equals a stepped one bit for bit; a
-// row's query sits one dim per lane and is broadcast by readlane. With 8
-// rows the kernel is bound by its fp32 FMAs, not by the caches' bytes: 3568
-// rows x 12 heads take 0.66 ms per layer, one row per workgroup 2.04 ms.
-constexpr int XR = 8;
-
 template <class T> struct Packed;  // loads kept in their storage type until used
 template <> struct Packed<bf16> {
     static constexpr int W = 2;
@@ -1139,6 +1129,14 @@ template <> struct Packed<bf16> {
             w[i / 2] = u.x;
             w[i / 2 + 1] = u.y;
         }
+    }
+    static __device__ __forceinline__ void ld2(const bf16* p, uint32_t* w) {
+        w[0] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(p));
+    }
+    static __device__ __forceinline__ void ld4(const bf16* p, uint32_t* w) {
+        const u32x2 u = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+        w[0] = u.x;
+        w[1] = u.y;
     }
     static __device__ __forceinline__ float at(const uint32_t* w, int i) {
         return __uint_as_float(i & 1 ? w[i / 2] & 0xffff0000u : w[i / 2] << 16);
@@ -1152,8 +1150,115 @@ template <> struct Packed<float> {
             w[i] = u.x; w[i + 1] = u.y; w[i + 2] = u.z; w[i + 3] = u.w;
         }
     }
+    static __device__ __forceinline__ void ld2(const float* p, uint32_t* w) {
+        const u32x2 u = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p));
+        w[0] = u.x;
+        w[1] = u.y;
+    }
+    static __device__ __forceinline__ void ld4(const float* p, uint32_t* w) {
+        const u32x4 u = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+        w[0] = u.x; w[1] = u.y; w[2] = u.z; w[3] = u.w;
+    }
     static __device__ __forceinline__ float at(const uint32_t* w, int i) { return __uint_as_float(w[i]); }
 };
+
+// Few rows: the same cross-attention with a workgroup of its own per
+// 256-position chunk. One CU draws some 45 bytes per ns from memory, so with
+// a workgroup per (row, head) and fewer of them than CUs a launch takes 11 us
+// for the 384 KB of one, however few there are. Here CW times as many
+// workgroups have all their loads in flight, which makes a layer's step 4 us
+// shorter (15 us in fp32) at one row. The chunks' results go to part / ml and
+// are merged by the output projection that reads them (skinny_merge_kernel),
+// which costs no launch of its own. Lane l of
+// wave f holds positions 128 f + 2 l, + 1 of the chunk for the scores and dims
+// 32 f + 4 (l % 8) .. + 3 for P V; every sum has cross_attn_kernel's operations
+// in its order, so the result is the same bit for bit.
+struct CrossPart {
+    float* part;  // [n][H][CW][64] unnormalised outputs of the chunks
+    float2* ml;   // [n][H][CW] their maximum and sum of weights
+};
+constexpr int CROSS_PART_FLOATS = CW * 66;  // per row and head
+// (row, head) pairs up to which the split pays: a decoder layer's step in us
+// without / with it, large (20 heads) 59.3 / 55.1 at 20 pairs, 60.3 / 59.1 at
+// 80, 60.5 / 60.9 at 100; small 47.7 / 43.2 at 12, 49.8 / 49.1 at 96, 50.3 /
+// 50.8 at 120; base 48.1 / 46.1 at 80; fp32 tiny 62.0 / 46.6 at 6, 67.9 / 59.4
+// at 96 (16 rows).
+template <class T> constexpr int CROSS_SPLIT_MAX = sizeof(T) == 2 ? 80 : 96;
+
+template <class T>
+__global__ __launch_bounds__(128) void cross_attn_split_kernel(DecAttnArgs a, CrossPart out) {
+    typedef Packed<T> P;
+    __shared__ float ps[256];
+    __shared__ float mw[2];
+    const int h = blockIdx.x, r = blockIdx.y, w = blockIdx.z, lane = threadIdx.x & 63, f = threadIdx.x >> 6;
+    if (a.stamp && threadIdx.x == 0) atomicMin(a.stamp, (unsigned long long)__builtin_amdgcn_s_memrealtime());
+    const int slot = a.list[r];
+    const float qv = ldf(reinterpret_cast<const T*>(a.q) + (long long)r * a.d + h * 64 + lane);
+    const long long head = (long long)slot * a.H + h;
+    const T* kt = reinterpret_cast<const T*>(a.kt) + head * 64 * a.TP;
+    const T* vv = reinterpret_cast<const T*>(a.v) + head * a.TP * 64;
+    const int start = 256 * w, p0 = start + 128 * f + 2 * lane, nloc = min(256, N_CTX - start);
+    const int dg = lane & 7, pg = lane >> 3;
+    uint32_t kv[64][2 / P::W], vr[32][4 / P::W];
+#pragma unroll
+    for (int j = 0; j < 64; ++j) P::ld2(kt + (long long)j * a.TP + p0, kv[j]);
+#pragma unroll
+    for (int u = 0; u < 32; ++u)
+        P::ld4(vv + (long long)(start + min(pg + 8 * u, nloc - 1)) * 64 + 32 * f + 4 * dg, vr[u]);
+    float s[2] = {0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+        const float qj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(qv), j));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) s[i] = fmaf(qj, P::at(kv[j], i), s[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) s[i] = (p0 + i < N_CTX) ? s[i] * LOG2E : -INFINITY;
+    const float wm = wave_max(fmaxf(s[0], s[1]));
+    if (lane == 0) mw[f] = wm;
+    __syncthreads();
+    const float mx = fmaxf(mw[0], mw[1]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) ps[128 * f + 2 * lane + i] = (p0 + i < N_CTX) ? exp2_softmax(s[i] - mx) : 0.f;
+    __syncthreads();
+    const long long e = ((long long)r * a.H + h) * CW + w;
+    if (f == 0) {  // the chunk's sum, four consecutive weights per lane
+        float lsum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lsum += ps[lane * 4 + i];
+        lsum = wave_sum(lsum);
+        if (lane == 0) out.ml[e] = make_float2(mx, lsum);
+    }
+    float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < 32; ++u) {
+        const int pp = pg + 8 * u;
+        const float pw = pp < nloc ? ps[pp] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = fmaf(pw, P::at(vr[u], i), o[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        o[i] += __shfl_xor(o[i], 8, 64);
+        o[i] += __shfl_xor(o[i], 16, 64);
+        o[i] += __shfl_xor(o[i], 32, 64);
+    }
+    if (lane < 8) st4(out.part + e * 64 + 32 * f + 4 * dg, o[0], o[1], o[2], o[3]);
+    if (a.stamp) {
+        __syncthreads();
+        if (threadIdx.x == 0) atomicMax(a.stamp + 1, (unsigned long long)__builtin_amdgcn_s_memrealtime());
+    }
+}
+
+// Prefill: the same cross-attention for up to XR rows of one slot per
+// workgroup, so that the slot's keys and values are read once for all of
+// them (one row at a time, 223 prompt positions read 384 KB per head 223
+// times). Every result is computed with cross_attn_kernel's operations in
+// its order, so a prefilled position equals a stepped one bit for bit; a
+// row's query sits one dim per lane and is broadcast by readlane. With 8
+// rows the kernel is bound by its fp32 FMAs, not by the caches' bytes: 3568
+// rows x 12 heads take 0.66 ms per layer, one row per workgroup 2.04 ms.
+constexpr int XR = 8;
 
 // groups[g] = first row of group g; groups[g + 1] - groups[g] <= XR rows of one slot
 template <class T>
@@ -1693,6 +1798,83 @@ __global__ __launch_bounds__(256) void many_kernel(const T* __restrict__ W, cons
 // CUs; below that the one-tile workgroups spread better.
 inline bool many_rows(int MA, int KS, int groups) { return MA % 128 == 0 && MA / 128 * KS * groups >= 128; }
 
+// skinny_kernel for up to 16 rows whose activations are a split
+// cross-attention's chunk results: a lane merges its fragment's elements
+// (cross_attn_kernel's last step, in its order) instead of loading them.
+// Reduction columns are head h's dims at 64 h; U k-steps per wave cover its
+// share of the Kc columns.
+template <class T, int U, class Epi>
+__global__ __launch_bounds__(256) void skinny_merge_kernel(const T* __restrict__ W, CrossPart x, int H, int nks_tot,
+                                                           int MA, int n, int Kc, Epi epi) {
+    typedef typename Frag<T>::type frag;
+    constexpr int EL = 16 / sizeof(T), PER = 64 / KSTEP<T>;  // k-steps per head
+    __shared__ float red[3 * 4 * 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int fr = lane & 15, fc = lane >> 4, i = blockIdx.x * 16 + fc * 4;
+    const int nks = Kc / KSTEP<T>, s_base = blockIdx.y * nks;
+    EpiPre pre;
+    if (wave == 0 && i < MA && fr < n) pre = epi.pre(i, fr, blockIdx.y);
+    frag a[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+        a[q] = *reinterpret_cast<const frag*>(
+            W + (((long long)blockIdx.x * nks_tot + s_base + min(wave + 4 * q, nks - 1)) * 64 + lane) * EL);
+    mfma_f32x4 acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+        if (wave + 4 * q < nks) {
+            const int st = s_base + wave + 4 * q, h = st / PER, dim = (st % PER) * KSTEP<T> + fc * EL;
+            frag b{};
+            if (fr < n) {
+                const long long e = ((long long)fr * H + h) * CW;
+                float2 ml[CW];
+                float4 p[CW][EL / 4];
+#pragma unroll
+                for (int c = 0; c < CW; ++c) {
+                    ml[c] = x.ml[e + c];
+#pragma unroll
+                    for (int k = 0; k < EL / 4; ++k) p[c][k] = ld4(x.part + (e + c) * 64 + dim + 4 * k);
+                }
+                float M = ml[0].x;
+#pragma unroll
+                for (int c = 1; c < CW; ++c) M = fmaxf(M, ml[c].x);
+                float L = 0.f, v[EL] = {};
+#pragma unroll
+                for (int c = 0; c < CW; ++c) {
+                    const float wgt = exp2_softmax(ml[c].x - M);
+                    L += wgt * ml[c].y;
+#pragma unroll
+                    for (int k = 0; k < EL / 4; ++k) {
+                        v[4 * k] += wgt * p[c][k].x;
+                        v[4 * k + 1] += wgt * p[c][k].y;
+                        v[4 * k + 2] += wgt * p[c][k].z;
+                        v[4 * k + 3] += wgt * p[c][k].w;
+                    }
+                }
+                T t[EL];
+#pragma unroll
+                for (int k = 0; k < EL; ++k) stf(&t[k], v[k] / L);
+                b = __builtin_bit_cast(frag, t);
+            }
+            acc = Frag<T>::mma(a[q], b, acc);
+        }
+    }
+    if (wave > 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) red[((wave - 1) * 4 + k) * 64 + lane] = acc[k];
+    }
+    __syncthreads();
+    if (wave > 0 || i >= MA || fr >= n) return;
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = acc[k];
+#pragma unroll
+        for (int w = 0; w < 3; ++w) v[k] += red[(w * 4 + k) * 64 + lane];
+    }
+    epi(i, fr, blockIdx.y, v[0], v[1], v[2], v[3], pre);
+}
+
 // Waves per workgroup of a residual projection (whole reduction in one
 // workgroup): twice the usual, to keep more loads in flight. The same for
 // every row count, since the waves' k-step split fixes the summation order.
@@ -1769,6 +1951,25 @@ inline void skinny(const T* W, int MA, const T* X, int n, int K, int KS, const E
     WMI_SKINNY_NT(n, WMI_SKINNY_U(Kc / KSTEP<T>, hipLaunchKernelGGL((skinny_kernel<T, 1, NT, U, Epi>),
                                                                     dim3((MA + 15) / 16, KS, groups), dim3(256), 0, st,
                                                                     W, X, nks_tot, MA, n, Kc, epi)));
+}
+
+// skinny() on a split cross-attention's chunk results (n <= 16 rows).
+template <class T, class Epi>
+inline void skinny_merge(const T* W, int MA, const CrossPart& x, int H, int n, int K, int KS, const Epi& epi,
+                         hipStream_t st) {
+    const int Kc = K / KS, nks = Kc / KSTEP<T>;
+    if (KS < 1 || K % (KSTEP<T> * KS) || n <= 0 || n > 16 || MA <= 0 || nks > 64)
+        throw ArgError(-1, "skinny_merge: unsupported shape");
+    const dim3 grid((MA + 15) / 16, KS);
+    auto launch = [&](auto u) {
+        hipLaunchKernelGGL((skinny_merge_kernel<T, decltype(u)::value, Epi>), grid, dim3(256), 0, st, W, x, H,
+                           K / KSTEP<T>, MA, n, Kc, epi);
+    };
+    const int u = (nks + 3) / 4;
+    if (u <= 2) launch(std::integral_constant<int, 2>{});
+    else if (u <= 4) launch(std::integral_constant<int, 4>{});
+    else if (u <= 8) launch(std::integral_constant<int, 8>{});
+    else launch(std::integral_constant<int, 16>{});
 }
 
 // ------------------------------------------------------------- CTC greedy decoding
