@@ -12,10 +12,11 @@
 // gemm_bf16: bf16 inputs, v_mfma_f32_16x16x32_bf16 with fp32 accumulation,
 //   K tiles of 32 streamed into an LDS ring with direct global->LDS loads
 //   (no staging registers), 16-byte chunks XOR-swizzled against bank
-//   conflicts. Two tilings: 256x256 tiles, 8 waves of 128x64, a 4-stage ring
-//   (one workgroup per CU), for K > 1024; 256x128 tiles, 8 waves of 64x64, a
-//   3-stage ring (two workgroups per CU), for K <= 1024. Tiles are mapped to
-//   the XCDs so that workgroups sharing an L2 share operand tiles.
+//   conflicts. Tiles of 256x256 (8 waves of 128x64, a 4-stage ring, one
+//   workgroup per CU), 256x128 (8 waves of 64x64, a 3-stage ring, two per CU),
+//   128x128 and 64x64, chosen by the number of workgroups they give; a
+//   result's sum is the same in all of them. Tiles are mapped to the XCDs so
+//   that workgroups sharing an L2 share operand tiles.
 //   Requires K % 64 == 0, MA % 4 == 0, 16-byte aligned rows (lda, ldb % 8 == 0).
 // gemm_f32: fp32 inputs on v_mfma_f32_16x16x4_f32 for the fp32 model, 64x64 or
 //   128x128 tiles. Requires K % 32 == 0 and 16-byte aligned rows.
@@ -280,59 +281,45 @@ inline void lds_limit(const void* f, int bytes, std::atomic<uint64_t>& done) {
     done.fetch_or(bit);
 }
 
-template <class Epi>
-inline void gemm_bf16(const bf16* A, int lda, long long sA, const bf16* B, int ldb, long long sB,
-                      int MA, int MB, int K, int batch, const Epi& epi, hipStream_t st) {
-    if (K % 64 || MA % 4 || lda % 8 || ldb % 8 || MA <= 0 || MB <= 0 || batch <= 0)
-        throw ArgError(-1, "gemm_bf16: unsupported shape");
-    const int tilesA = (MA + gb::BM - 1) / gb::BM, tilesB = (MB + gb::BN - 1) / gb::BN;
-    // Short reductions (K <= 1024) take the 256 x 128 tiles, two workgroups
-    // per CU, whose prologues and epilogues overlap; longer ones the
-    // 256 x 256 tiles. WHISPER_GEMM_H=0/1 forces one.
-    static const int force = [] {
-        const char* g = getenv("WHISPER_GEMM_H");
-        return g ? (g[0] == '1' ? 1 : 0) : -1;
-    }();
-    if (force == 1 || (force < 0 && K <= 1024)) {
-        static std::atomic<uint64_t> done_h{0};  // one per epilogue instantiation
-        lds_limit(reinterpret_cast<const void*>(&gemm_bf16_h_kernel<Epi>), gh::LDS_BYTES, done_h);
-        const int tb2 = (MB + gh::BN - 1) / gh::BN;
-        dim3 grid(tilesA * tb2, 1, batch);
-        hipLaunchKernelGGL((gemm_bf16_h_kernel<Epi>), grid, dim3(gh::THREADS), gh::LDS_BYTES, st, A, lda, sA, B,
-                           ldb, sB, MA, MB, K, tilesA, epi);
-        return;
-    }
-    static std::atomic<uint64_t> done{0};
-    lds_limit(reinterpret_cast<const void*>(&gemm_bf16_kernel<Epi>), gb::LDS_BYTES, done);
-    dim3 grid(tilesA * tilesB, 1, batch);
-    hipLaunchKernelGGL((gemm_bf16_kernel<Epi>), grid, dim3(gb::THREADS), gb::LDS_BYTES, st, A, lda,
-                       sA, B, ldb, sB, MA, MB, K, tilesA, epi);
-}
-
-// ----------------------------------------------------------------- fp32 MFMA
+// ----------------------------------------------------------------- 64 x 64 and 128 x 128 tiles
 //
-// C = A B^T in fp32 on v_mfma_f32_16x16x4_f32 (fp32 products and sums): a
-// workgroup tile of 32 WT x 32 WT, 4 waves of 16 WT x 16 WT, K tiles of 32
-// streamed into an LDS ring of NS stages with direct global->LDS loads.
-// A lane reads 16 bytes (four k) of a row per fragment and the four values
-// feed four MFMAs, so MFMA step r reduces over k = 4 (lane / 16) + r of a
-// 16-wide slice in both operands. LDS rows are 128 bytes; the 16-byte chunk c
-// of row r sits at c ^ ((r >> 1) & 7), so the 16 rows of one read pass fill
-// the 64 banks once.
-// Bound by the fp32 matrix rate (each 16x16x4 takes 32 cycles of a SIMD): a
-// fragment read pair feeds 4 WT MFMAs, so LDS and L2 are far from their
-// limits with either tile. 13500 x 1536 x 384 with GELU: 153 us (104 TFLOP/s;
-// with vector FMAs 10500 rows took 374 us, 33 TFLOP/s); 1500 x 1536 x 384:
-// 29 us (vector FMAs 74 us).
-namespace gf {
-constexpr int BK = 32;
-}
+// C = A B^T with a workgroup tile of 32 WT x 32 WT, 4 waves of 16 WT x 16 WT,
+// for the fp32 model (fp32 products and sums on v_mfma_f32_16x16x4_f32) and
+// for the bf16 launches whose larger tiles would leave CUs without work. K
+// tiles are 128 bytes of a row (32 fp32 or 64 bf16 columns), streamed into an
+// LDS ring of NS stages with direct global->LDS loads; 16-byte chunk c of row
+// r sits at c ^ ((r >> 1) & 7), so the 16 rows of one read pass fill the 64
+// banks once. A lane reads 16 bytes of a row per fragment: eight k of one
+// bf16 MFMA, or four k that feed four fp32 MFMAs, step r reducing over
+// k = 4 (lane / 16) + r of a 16-wide slice in both operands. In bf16 a
+// result's sum is taken in the order of the larger tiles' kernels, so it is
+// the same bit for bit with every tile.
+// fp32 is bound by the matrix rate (a 16x16x4 takes 32 cycles of a SIMD):
+// 13500 x 1536 x 384 with GELU: 153 us (104 TFLOP/s; with vector FMAs 10500
+// rows took 374 us, 33 TFLOP/s); 1500 x 1536 x 384: 29 us (74 us).
+template <class T> struct Frag;  // 16 bytes of an operand per lane
+template <> struct Frag<bf16> {
+    typedef mfma_bf16x8 type;
+    static constexpr int STEPS = 1;  // MFMAs of a fragment pair
+    static __device__ __forceinline__ mfma_f32x4 step(type a, type b, mfma_f32x4 c, int) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct Frag<float> {
+    typedef mfma_f32x4 type;
+    static constexpr int STEPS = 4;
+    static __device__ __forceinline__ mfma_f32x4 step(type a, type b, mfma_f32x4 c, int r) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], c, 0, 0, 0);
+    }
+};
 
-template <int WT, int NS, class Epi>
-__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restrict__ A, int lda, long long sA,
-                                                          const float* __restrict__ B, int ldb, long long sB, int MA,
-                                                          int MB, int K, int tilesA, Epi epi) {
+template <class T, int WT, int NS, class Epi>
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const T* __restrict__ A, int lda, long long sA,
+                                                           const T* __restrict__ B, int ldb, long long sB, int MA,
+                                                           int MB, int K, int tilesA, Epi epi) {
+    typedef typename Frag<T>::type frag;
     constexpr int TB = 32 * WT, OP_BYTES = TB * 128, STAGE = 2 * OP_BYTES;
+    constexpr int BK = 128 / sizeof(T), EL = 16 / sizeof(T);
     extern __shared__ __align__(16) unsigned char lds[];
     const int z = blockIdx.z;
     A += (long long)z * sA;
@@ -347,19 +334,19 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
     // Direct loads: wave w fills rows 8 WT w .. 8 WT (w + 1) - 1 of both tiles
     // with WT + WT instructions of 8 rows; lane i loads the logical chunk
     // stored at position i % 8 of row i / 8.
-    const float* ga[4];  // WT of them
-    const float* gp[4];
+    const unsigned char* ga[4];  // WT of them
+    const unsigned char* gp[4];
 #pragma unroll
     for (int s = 0; s < WT; ++s) {
         const int r = wave * 8 * WT + s * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ((r >> 1) & 7);
-        ga[s] = A + (long long)min(a0 + r, MA - 1) * lda + c * 4;
-        gp[s] = B + (long long)min(b0 + r, MB - 1) * ldb + c * 4;
+        ga[s] = reinterpret_cast<const unsigned char*>(A + (long long)min(a0 + r, MA - 1) * lda + c * EL);
+        gp[s] = reinterpret_cast<const unsigned char*>(B + (long long)min(b0 + r, MB - 1) * ldb + c * EL);
     }
-#define WMI_ISSUEF(KT)                                                                                    \
+#define WMI_ISSUET(KT)                                                                                    \
     do {                                                                                                  \
         int sa_ = ((KT) % NS) * STAGE + wave * 8 * WT * 128, sb_ = sa_ + OP_BYTES;                        \
-        const int k_ = (KT) * gf::BK;                                                                     \
+        const int k_ = (KT) * 128;                                                                        \
         _Pragma("unroll") for (int s = 0; s < WT; ++s) {                                                 \
             __builtin_amdgcn_global_load_lds(ga[s] + k_, lds + sa_ + s * 1024, 16, 0, 0);                 \
             __builtin_amdgcn_global_load_lds(gp[s] + k_, lds + sb_ + s * 1024, 16, 0, 0);                 \
@@ -371,10 +358,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
 #pragma unroll
         for (int j = 0; j < WT; ++j) acc[i][j] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int nk = K / gf::BK;
+    const int nk = K / BK;
 #pragma unroll
     for (int q = 0; q < NS - 1; ++q)
-        if (q < nk) WMI_ISSUEF(q);
+        if (q < nk) WMI_ISSUET(q);
     for (int kt = 0; kt < nk; ++kt) {
         // tile kt has landed once only the later tiles' 2 WT loads are pending
         const int later = min(nk - 1 - kt, NS - 2);
@@ -383,47 +370,96 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float* __restric
         else if (later == 1) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(4));
         else __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
         __builtin_amdgcn_s_barrier();
-        if (kt + NS - 1 < nk) WMI_ISSUEF(kt + NS - 1);
+        if (kt + NS - 1 < nk) WMI_ISSUET(kt + NS - 1);
         const unsigned char* stage = lds + (kt % NS) * STAGE;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            mfma_f32x4 fa[WT], fb[WT];
+            frag fa[WT], fb[WT];
 #pragma unroll
             for (int i = 0; i < WT; ++i) {
                 const int ra = wa + i * 16 + fr, rb = wb + i * 16 + fr, c = 4 * h + fc;
-                fa[i] = *reinterpret_cast<const mfma_f32x4*>(stage + ra * 128 + ((c ^ ((ra >> 1) & 7)) << 4));
-                fb[i] = *reinterpret_cast<const mfma_f32x4*>(stage + OP_BYTES + rb * 128 + ((c ^ ((rb >> 1) & 7)) << 4));
+                fa[i] = *reinterpret_cast<const frag*>(stage + ra * 128 + ((c ^ ((ra >> 1) & 7)) << 4));
+                fb[i] = *reinterpret_cast<const frag*>(stage + OP_BYTES + rb * 128 + ((c ^ ((rb >> 1) & 7)) << 4));
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int r = 0; r < Frag<T>::STEPS; ++r)
 #pragma unroll
                 for (int j = 0; j < WT; ++j)
 #pragma unroll
-                    for (int i = 0; i < WT; ++i)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][r], fb[j][r], acc[i][j], 0, 0, 0);
+                    for (int i = 0; i < WT; ++i) acc[i][j] = Frag<T>::step(fa[i], fb[j], acc[i][j], r);
         }
     }
-#undef WMI_ISSUEF
+#undef WMI_ISSUET
     tile_epilogue(epi, acc, a0 + wa, b0 + wb, fr, fc, z, MA, MB, a0 + TB <= MA && b0 + TB <= MB);
+}
+
+template <class T, int WT, int NS, class Epi>
+inline void gemm_tile(const T* A, int lda, long long sA, const T* B, int ldb, long long sB, int MA, int MB, int K,
+                      int batch, const Epi& epi, hipStream_t st) {
+    const int ta = (MA + 32 * WT - 1) / (32 * WT), tb = (MB + 32 * WT - 1) / (32 * WT);
+    hipLaunchKernelGGL((gemm_tile_kernel<T, WT, NS, Epi>), dim3(ta * tb, 1, batch), dim3(256), NS * 2 * 32 * WT * 128, st,
+                       A, lda, sA, B, ldb, sB, MA, MB, K, ta, epi);
 }
 
 template <class Epi>
 inline void gemm_f32(const float* A, int lda, long long sA, const float* B, int ldb, long long sB, int MA, int MB,
                      int K, int batch, const Epi& epi, hipStream_t st) {
     // rows i0..i0+3 past MA reach the epilogue when MA % 4 != 0: it must drop them
-    if (MA <= 0 || MB <= 0 || K <= 0 || K % gf::BK || lda % 4 || ldb % 4 || sA % 4 || sB % 4 || batch <= 0)
+    if (MA <= 0 || MB <= 0 || K <= 0 || K % 32 || lda % 4 || ldb % 4 || sA % 4 || sB % 4 || batch <= 0)
         throw ArgError(-1, "gemm_f32: unsupported shape");
     // 128 x 128 tiles once they fill the chip's 512 workgroup slots (two per
     // CU); below that the 64 x 64 tiles' four times as many workgroups.
-    const int t128a = (MA + 127) / 128, t128b = (MB + 127) / 128;
-    if ((long long)t128a * t128b * batch >= 512) {
-        hipLaunchKernelGGL((gemm_f32_kernel<4, 2, Epi>), dim3(t128a * t128b, 1, batch), dim3(256), 2 * 2 * 128 * 128, st,
-                           A, lda, sA, B, ldb, sB, MA, MB, K, t128a, epi);
-    } else {
-        const int ta = (MA + 63) / 64, tb = (MB + 63) / 64;
-        hipLaunchKernelGGL((gemm_f32_kernel<2, 4, Epi>), dim3(ta * tb, 1, batch), dim3(256), 4 * 2 * 64 * 128, st, A,
-                           lda, sA, B, ldb, sB, MA, MB, K, ta, epi);
+    if ((long long)((MA + 127) / 128) * ((MB + 127) / 128) * batch >= 512)
+        gemm_tile<float, 4, 2>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
+    else
+        gemm_tile<float, 2, 4>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
+}
+
+template <class Epi>
+inline void gemm_bf16(const bf16* A, int lda, long long sA, const bf16* B, int ldb, long long sB,
+                      int MA, int MB, int K, int batch, const Epi& epi, hipStream_t st) {
+    if (K % 64 || MA % 4 || lda % 8 || ldb % 8 || MA <= 0 || MB <= 0 || batch <= 0)
+        throw ArgError(-1, "gemm_bf16: unsupported shape");
+    // The tile by the number of workgroups it gives 256 CUs (measured alone
+    // on the encoder's launches of 1 to 32 segments, d = 512, 768 and 1280):
+    //  - 64 x 64 while 128 x 128 tiles are fewer than 144 (d = 1280, one
+    //    segment, fc2: 36.8 us against 56.5 with 128, 133.7 with 256);
+    //  - for K <= 640 with at least 750 of them, 256 x 128, two workgroups per
+    //    CU (d = 512, 32 segments, fc1: 150 against 162 and 153 us);
+    //  - for longer K, 256 x 256 where its last round of one per CU leaves less
+    //    than a tenth of the time idle (d = 1280, 8 segments, fc2: 149 against
+    //    165 us with 128);
+    //  - 128 x 128, two per CU, otherwise (5 segments, QK: 61.7 against 82.9 us
+    //    with 256; 16 segments at d = 768, fc2: 132 against 181 us).
+    // WHISPER_GEMM_TILE = 64, 128, 256 or 384 (256 x 128) forces one.
+    static const int force = [] {
+        const char* g = getenv("WHISPER_GEMM_TILE");
+        return g ? atoi(g) : 0;
+    }();
+    const int tilesA = (MA + gb::BM - 1) / gb::BM, tilesB = (MB + gb::BN - 1) / gb::BN;
+    const long long t128 = (long long)((MA + 127) / 128) * ((MB + 127) / 128) * batch;
+    const long long t384 = (long long)tilesA * ((MB + gh::BN - 1) / gh::BN) * batch;
+    const long long t256 = (long long)tilesA * tilesB * batch;
+    const int tile = force ? force
+                   : t128 < 144 ? 64
+                   : K <= 640 ? (t384 >= 750 ? 384 : 128)
+                   : t256 * 10 >= (t256 + 255) / 256 * 256 * 9 ? 256 : 128;
+    if (tile == 64) return gemm_tile<bf16, 2, 4>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
+    if (tile == 128) return gemm_tile<bf16, 4, 2>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
+    if (tile == 384) {
+        static std::atomic<uint64_t> done_h{0};  // one per epilogue instantiation
+        lds_limit(reinterpret_cast<const void*>(&gemm_bf16_h_kernel<Epi>), gh::LDS_BYTES, done_h);
+        const int tb2 = (MB + gh::BN - 1) / gh::BN;
+        dim3 grid(tilesA * tb2, 1, batch);
+        hipLaunchKernelGGL((gemm_bf16_h_kernel<Epi>), grid, dim3(gh::THREADS), gh::LDS_BYTES, st, A, lda, sA, B,
+                           ldb, sB, MA, MB, K, tilesA, epi);
+        return;
     }
+    static std::atomic<uint64_t> done{0};
+    lds_limit(reinterpret_cast<const void*>(&gemm_bf16_kernel<Epi>), gb::LDS_BYTES, done);
+    dim3 grid(tilesA * tilesB, 1, batch);
+    hipLaunchKernelGGL((gemm_bf16_kernel<Epi>), grid, dim3(gb::THREADS), gb::LDS_BYTES, st, A, lda,
+                       sA, B, ldb, sB, MA, MB, K, tilesA, epi);
 }
 
 }  // namespace wmi

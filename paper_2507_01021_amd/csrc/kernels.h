@@ -1401,21 +1401,12 @@ __global__ void stamp_reset_kernel(unsigned long long* __restrict__ s, int n) {
 // took 37 us each (d = 384, 7 rows) as a GEMM of 64 x 64 vector-FMA tiles and
 // 12 us on its MFMA tiles; here 3.4-3.8 us, a launch's latency. NW waves per workgroup
 // (4, or more for long reductions), red: (NW - 1) * RT * NT * 4 * 64 floats.
-template <class T> struct Frag;  // 16 bytes of an operand per lane
-template <> struct Frag<bf16> {
-    typedef mfma_bf16x8 type;
-    static __device__ __forceinline__ mfma_f32x4 mma(type a, type b, mfma_f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
-};
-template <> struct Frag<float> {
-    typedef mfma_f32x4 type;
-    static __device__ __forceinline__ mfma_f32x4 mma(type a, type b, mfma_f32x4 c) {
+template <class T>
+__device__ __forceinline__ mfma_f32x4 frag_mma(typename Frag<T>::type a, typename Frag<T>::type b, mfma_f32x4 c) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b[r], c, 0, 0, 0);
-        return c;
-    }
-};
+    for (int r = 0; r < Frag<T>::STEPS; ++r) c = Frag<T>::step(a, b, c, r);
+    return c;
+}
 
 template <class T, int RT, int NT, int U, int NW = 4>
 __device__ __forceinline__ void skinny_core(const T* __restrict__ W, const T* __restrict__ X, int nks_tot, int n,
@@ -1456,7 +1447,7 @@ __device__ __forceinline__ void skinny_core(const T* __restrict__ W, const T* __
                 for (int t = 0; t < RT; ++t)
 #pragma unroll
                     for (int u = 0; u < NT; ++u)
-                        acc[t][u] = Frag<T>::mma(a[q][t], b[q][u], acc[t][u]);
+                        acc[t][u] = frag_mma<T>(a[q][t], b[q][u], acc[t][u]);
             }
         }
     }
@@ -1771,7 +1762,7 @@ __global__ __launch_bounds__(256) void many_kernel(const T* __restrict__ W, cons
 #pragma unroll
                     for (int t = 0; t < RT; ++t)
 #pragma unroll
-                        for (int u = 0; u < NT; ++u) acc[t][u] = Frag<T>::mma(a[q][t], b[q][u], acc[t][u]);
+                        for (int u = 0; u < NT; ++u) acc[t][u] = frag_mma<T>(a[q][t], b[q][u], acc[t][u]);
                 }
             }
         }
@@ -1856,7 +1847,7 @@ __global__ __launch_bounds__(256) void skinny_merge_kernel(const T* __restrict__
                 for (int k = 0; k < EL; ++k) stf(&t[k], v[k] / L);
                 b = __builtin_bit_cast(frag, t);
             }
-            acc = Frag<T>::mma(a[q], b, acc);
+            acc = frag_mma<T>(a[q], b, acc);
         }
     }
     if (wave > 0) {
