@@ -10,14 +10,14 @@
 // is A so that the four consecutive i are the contiguous output dimension.
 //
 // gemm_bf16: bf16 inputs, v_mfma_f32_16x16x32_bf16 with fp32 accumulation,
-//   K tiles of 32 streamed into an LDS ring with direct global->LDS loads
-//   (no staging registers), 16-byte chunks XOR-swizzled against bank
-//   conflicts. Tiles of 256x256 (8 waves of 128x64, a 4-stage ring, one
-//   workgroup per CU), 256x128 (8 waves of 64x64, a 3-stage ring, two per CU),
+//   K tiles streamed into LDS with direct global->LDS loads (no staging
+//   registers), 16-byte chunks XOR-swizzled against bank conflicts. Tiles of
+//   256x256 (8 waves of 128x64 in two alternating groups, one workgroup per
+//   CU), 256x128 (8 waves of 64x64, a 3-stage ring, two per CU),
 //   128x128 and 64x64, chosen by the number of workgroups they give; a
 //   result's sum is the same in all of them. Tiles are mapped to the XCDs so
 //   that workgroups sharing an L2 share operand tiles.
-//   Requires K % 64 == 0, MA % 4 == 0, 16-byte aligned rows (lda, ldb % 8 == 0).
+//   Requires K % 64 == 0, K >= 128, MA % 4 == 0, 16-byte aligned rows (lda, ldb % 8 == 0).
 // gemm_f32: fp32 inputs on v_mfma_f32_16x16x4_f32 for the fp32 model, 64x64 or
 //   128x128 tiles. Requires K % 32 == 0 and 16-byte aligned rows.
 #pragma once
@@ -34,14 +34,13 @@ typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------------ bf16 MFMA
 
 namespace gb {
-constexpr int BM = 256;   // A rows per workgroup
-constexpr int BN = 256;   // B rows per workgroup
-constexpr int BK = 32;    // K per LDS stage
-constexpr int NS = 4;     // LDS stages
+constexpr int BM = 256;       // A rows per workgroup
+constexpr int BN = 256;       // B rows per workgroup
+constexpr int BK = 64;        // K per LDS buffer
 constexpr int THREADS = 512;  // 8 waves
-constexpr int TILE_BYTES = BM * BK * 2;        // one operand tile of a stage (16 KiB)
-constexpr int STAGE_BYTES = 2 * TILE_BYTES;    // A and B tiles (32 KiB)
-constexpr int LDS_BYTES = NS * STAGE_BYTES;    // 128 KiB
+constexpr int OP_BYTES = 256 * BK * 2;         // one operand tile of a buffer (32 KiB)
+constexpr int STAGE_BYTES = 2 * OP_BYTES;      // A and B tiles (64 KiB)
+constexpr int LDS_BYTES = 2 * STAGE_BYTES;     // two buffers (128 KiB)
 }  // namespace gb
 
 // Byte offset of 16-byte chunk c (0..3) of row r in a [rows][32] bf16 LDS tile:
@@ -112,84 +111,174 @@ __device__ __forceinline__ void tile_epilogue(const Epi& epi, const mfma_f32x4 (
 }
 
 // C = A B^T for A [MA][K], B [MB][K] (bf16, row-major, batched over z):
-// a 256 x 256 workgroup tile, 8 waves (2 per SIMD) of 128 x 64 each on
-// 16x16x32 MFMAs, so one wave's MFMAs run while the other waits on its LDS
-// reads or the stage barrier. Operands go global -> LDS directly through a
-// 4-stage ring of 32-wide K tiles.
+// a 256 x 256 workgroup tile, 8 waves of 128 x 64 on 16x16x32 MFMAs, K tiles
+// of 64 in two LDS buffers (128-byte rows, 16-byte chunk c of row r at
+// c ^ ((r >> 1) & 7)), filled by direct global->LDS loads.
+//
+// A CU reads LDS at 128 bytes per clock, and these wave tiles need as many
+// clocks of fragment reads as of MFMAs, so the two have to run side by side
+// all the time. The waves therefore work in two groups of four, one wave of
+// each per SIMD, half a phase apart: while one group runs the 16 MFMAs of a
+// phase, the other reads its next fragments and issues loads, and a barrier
+// swaps them. Raised priority keeps a group's MFMAs ahead of the other
+// group's reads. A K tile takes four phases, over the wave's quadrants
+//   (a0, b0) (a0, b1) (a1, b1) (a1, b0),
+// a0 / a1 being its 64-row halves and b0 / b1 its 32-row halves, so a phase
+// reads 12, 4, 8 and 0 fragments. The loads of tile t + 2 go into tile t's
+// buffer by halves (A rows with bit 6 = h, B rows with bit 5 = h), each two
+// phases after its half of tile t was read (the groups being one barrier
+// apart, every wave's reads have then completed) and 12 barriers before its
+// own first read; the vmcnt waits count exactly the later loads in flight.
+// In a result's sum k runs in order, as in every tile size.
+//
+// 48000 x 5120 x 1280 without an epilogue 446 us (1412 TFLOP/s) against
+// 528 us (1191) of a four-stage ring with one barrier per 32-wide K tile, in
+// which all waves read at once and then multiplied at once; with GELU 597
+// against 677 us; 48000 x 1280 x 5120 with the residual update 563 against
+// 662 us. What is left is mostly the epilogue, which nothing overlaps.
 template <class Epi>
-__global__ __launch_bounds__(512, 1) void gemm_bf16_kernel(
+__global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(
     const bf16* __restrict__ A, int lda, long long sA, const bf16* __restrict__ B, int ldb,
     long long sB, int MA, int MB, int K, int tilesA, Epi epi) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int z = blockIdx.z;
-    A += (long long)z * sA;
-    B += (long long)z * sB;
     int ta, tb;
     xcd_tile(blockIdx.x, tilesA, (int)(gridDim.x / tilesA), ta, tb);
     const int a0 = ta * gb::BM, b0 = tb * gb::BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wa = (wave & 1) * 128, wb = (wave >> 1) * 64;
     const int fr = lane & 15, fc = lane >> 4;
+    const unsigned char* pA = reinterpret_cast<const unsigned char*>(A + (long long)z * sA + (long long)a0 * lda);
+    const unsigned char* pB = reinterpret_cast<const unsigned char*>(B + (long long)z * sB + (long long)b0 * ldb);
 
-    // Direct loads: wave w fills rows 32 w .. 32 w + 31 of both operand tiles
-    // with 2 + 2 instructions of 16 rows x 64 B; lane i loads row 16 s + i / 4
-    // and the logical chunk stored at its physical position i % 4.
-    const int dr = lane >> 2;
-    const int dc = (lane & 3) ^ ((dr >> 1) & 3);
-    const bf16* ga[2];
-    const bf16* gp[2];
+    // Direct loads: of each half tile (128 rows) wave w fills the 8-row groups
+    // 2 w and 2 w + 1, one instruction each; lane i loads the logical chunk
+    // stored at position i % 8 of row i / 8. Offsets are from the tile's first
+    // row; rows past the matrix re-read its last one.
+    unsigned oa[2][2], ob[2][2];
+    int la[2][2], lb[2][2];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int r = wave * 32 + s * 16 + dr;
-        ga[s] = A + (long long)min(a0 + r, MA - 1) * lda + dc * 8;
-        gp[s] = B + (long long)min(b0 + r, MB - 1) * ldb + dc * 8;
-    }
-    const int ldsw = wave * 32 * 64;
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int g = wave * 2 + s;
+            const int ra = (g >> 3) * 128 + (g & 7) * 8 + 64 * h, rb = (g >> 2) * 64 + (g & 3) * 8 + 32 * h;
+            const int r = ra + (lane >> 3), q = rb + (lane >> 3);
+            oa[h][s] = (unsigned)(min(a0 + r, MA - 1) - a0) * (unsigned)(lda * 2) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+            ob[h][s] = (unsigned)(min(b0 + q, MB - 1) - b0) * (unsigned)(ldb * 2) + (((lane & 7) ^ ((q >> 1) & 7)) << 4);
+            la[h][s] = ra * 128;
+            lb[h][s] = gb::OP_BYTES + rb * 128;
+        }
+#define WMI_LOAD_A(H, T)                                                                       \
+    do {                                                                                       \
+        const int b_ = ((T) & 1) * gb::STAGE_BYTES;                                            \
+        const unsigned char* p_ = pA + (T) * 128;                                              \
+        __builtin_amdgcn_global_load_lds(p_ + oa[H][0], lds + b_ + la[H][0], 16, 0, 0);        \
+        __builtin_amdgcn_global_load_lds(p_ + oa[H][1], lds + b_ + la[H][1], 16, 0, 0);        \
+    } while (0)
+#define WMI_LOAD_B(H, T)                                                                       \
+    do {                                                                                       \
+        const int b_ = ((T) & 1) * gb::STAGE_BYTES;                                            \
+        const unsigned char* p_ = pB + (T) * 128;                                              \
+        __builtin_amdgcn_global_load_lds(p_ + ob[H][0], lds + b_ + lb[H][0], 16, 0, 0);        \
+        __builtin_amdgcn_global_load_lds(p_ + ob[H][1], lds + b_ + lb[H][1], 16, 0, 0);        \
+    } while (0)
+#define WMI_SWAP()                             \
+    do {                                       \
+        __builtin_amdgcn_sched_barrier(0);     \
+        __builtin_amdgcn_s_barrier();          \
+        __builtin_amdgcn_sched_barrier(0);     \
+    } while (0)
 
     mfma_f32x4 acc[8][4];
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
-
-#define WMI_ISSUE8(KT)                                                                                 \
-    do {                                                                                               \
-        const int st_ = ((KT) % gb::NS) * gb::STAGE_BYTES + ldsw;                                      \
-        const int k_ = (KT) * gb::BK;                                                                  \
-        _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                 \
-            __builtin_amdgcn_global_load_lds(ga[s] + k_, lds + st_ + s * 1024, 16, 0, 0);              \
-        _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                 \
-            __builtin_amdgcn_global_load_lds(gp[s] + k_, lds + st_ + gb::TILE_BYTES + s * 1024, 16, 0, 0); \
-    } while (0)
-
-    const int nk = K / gb::BK;
-    WMI_ISSUE8(0);
-    if (nk > 1) WMI_ISSUE8(1);
-    if (nk > 2) WMI_ISSUE8(2);
-    for (int kt = 0; kt < nk; ++kt) {
-        // tile kt has landed once only the 4-load groups of later tiles are pending
-        const int later = min(nk - 1 - kt, gb::NS - 2);
-        if (later >= 2) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(8));
-        else if (later == 1) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(4));
-        else __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
-        // every wave's part of tile kt is in LDS, and every wave is done with tile kt - 1
-        __builtin_amdgcn_s_barrier();
-        if (kt + gb::NS - 1 < nk) WMI_ISSUE8(kt + gb::NS - 1);
-        const unsigned char* stage = lds + (kt % gb::NS) * gb::STAGE_BYTES;
-        mfma_bf16x8 fa[8], fb[4];
+    int ra[2], rb[2];  // this lane's fragment bytes of the first row block, k-steps 0 and 1
 #pragma unroll
-        for (int i = 0; i < 8; ++i) fa[i] = *reinterpret_cast<const mfma_bf16x8*>(stage + swz32(wa + i * 16 + fr, fc));
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            fb[j] = *reinterpret_cast<const mfma_bf16x8*>(stage + gb::TILE_BYTES + swz32(wb + j * 16 + fr, fc));
-        __builtin_amdgcn_sched_barrier(0);  // every fragment read is issued ahead of the MFMAs
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    for (int s = 0; s < 2; ++s) {
+        ra[s] = (wa + fr) * 128 + (((4 * s + fc) ^ (fr >> 1)) << 4);
+        rb[s] = gb::OP_BYTES + (wb + fr) * 128 + (((4 * s + fc) ^ (fr >> 1)) << 4);
     }
-#undef WMI_ISSUE8
+    mfma_bf16x8 fa[4][2], fb0[2][2], fb1[2][2];
+#define WMI_READ_A(H)                                                                                          \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i) _Pragma("unroll") for (int s = 0; s < 2; ++s) fa[i][s] =     \
+        *reinterpret_cast<const mfma_bf16x8*>(stage + ra[s] + ((H) * 4 + i) * 2048)
+#define WMI_READ_B(F, H)                                                                                       \
+    _Pragma("unroll") for (int j = 0; j < 2; ++j) _Pragma("unroll") for (int s = 0; s < 2; ++s) F[j][s] =      \
+        *reinterpret_cast<const mfma_bf16x8*>(stage + rb[s] + ((H) * 2 + j) * 2048)
+#define WMI_MMA(F, AH, BH)                                                                                     \
+    do {                                                                                                       \
+        __builtin_amdgcn_sched_barrier(0);                                                                     \
+        __builtin_amdgcn_s_setprio(1);                                                                         \
+        _Pragma("unroll") for (int s = 0; s < 2; ++s) _Pragma("unroll") for (int j = 0; j < 2; ++j)           \
+            _Pragma("unroll") for (int i = 0; i < 4; ++i) acc[(AH) * 4 + i][(BH) * 2 + j] =                    \
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i][s], F[j][s], acc[(AH) * 4 + i][(BH) * 2 + j], 0, 0, 0); \
+        __builtin_amdgcn_s_setprio(0);                                                                         \
+        __builtin_amdgcn_sched_barrier(0);                                                                     \
+    } while (0)
+    constexpr int LGKM0 = 0xC07F;  // wait for every LDS read, for no vector-memory operation
+
+    const int nk = K / gb::BK;  // at least 2
+    WMI_LOAD_A(0, 0);
+    WMI_LOAD_B(0, 0);
+    WMI_LOAD_B(1, 0);
+    WMI_LOAD_A(1, 0);
+    WMI_LOAD_A(0, 1);
+    WMI_LOAD_B(0, 1);
+    WMI_LOAD_B(1, 1);
+    __builtin_amdgcn_s_waitcnt(WMI_VMCNT(10));  // a0 and b0 of tile 0
+    WMI_SWAP();
+    if (wave >= 4) WMI_SWAP();  // the second group starts half a phase later
+    for (int t = 0; t < nk; ++t) {
+        const unsigned char* stage = lds + (t & 1) * gb::STAGE_BYTES;
+        const bool last = t == nk - 1, last2 = t == nk - 2;
+        WMI_READ_B(fb0, 0);
+        WMI_READ_A(0);
+        if (!last) {
+            WMI_LOAD_A(1, t + 1);
+            __builtin_amdgcn_s_waitcnt(WMI_VMCNT(10));  // b1 of tile t
+        } else {
+            __builtin_amdgcn_s_waitcnt(WMI_VMCNT(2));
+        }
+        WMI_SWAP();
+        __builtin_amdgcn_s_waitcnt(LGKM0);
+        WMI_MMA(fb0, 0, 0);
+        WMI_SWAP();
+        WMI_READ_B(fb1, 1);
+        if (!last) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(8));  // a1 of tile t
+        else __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
+        WMI_SWAP();
+        __builtin_amdgcn_s_waitcnt(LGKM0);
+        WMI_MMA(fb1, 0, 1);
+        WMI_SWAP();
+        WMI_READ_A(1);
+        if (!last && !last2) {
+            WMI_LOAD_A(0, t + 2);
+            WMI_LOAD_B(0, t + 2);
+        }
+        WMI_SWAP();
+        __builtin_amdgcn_s_waitcnt(LGKM0);
+        WMI_MMA(fb1, 1, 1);
+        WMI_SWAP();
+        if (!last && !last2) {
+            WMI_LOAD_B(1, t + 2);
+            __builtin_amdgcn_s_waitcnt(WMI_VMCNT(10));  // a0 and b0 of tile t + 1
+        } else if (last2) {
+            __builtin_amdgcn_s_waitcnt(WMI_VMCNT(4));
+        }
+        WMI_SWAP();
+        WMI_MMA(fb0, 1, 0);
+        WMI_SWAP();
+    }
+    if (wave < 4) WMI_SWAP();  // as many barriers as the second group
+#undef WMI_LOAD_A
+#undef WMI_LOAD_B
+#undef WMI_SWAP
+#undef WMI_READ_A
+#undef WMI_READ_B
+#undef WMI_MMA
     tile_epilogue(epi, acc, a0 + wa, b0 + wb, fr, fc, z, MA, MB, a0 + gb::BM <= MA && b0 + gb::BN <= MB);
 }
 
@@ -418,19 +507,20 @@ inline void gemm_f32(const float* A, int lda, long long sA, const float* B, int 
 template <class Epi>
 inline void gemm_bf16(const bf16* A, int lda, long long sA, const bf16* B, int ldb, long long sB,
                       int MA, int MB, int K, int batch, const Epi& epi, hipStream_t st) {
-    if (K % 64 || MA % 4 || lda % 8 || ldb % 8 || MA <= 0 || MB <= 0 || batch <= 0)
+    if (K % 64 || K < 128 || MA % 4 || lda % 8 || ldb % 8 || MA <= 0 || MB <= 0 || batch <= 0)
         throw ArgError(-1, "gemm_bf16: unsupported shape");
     // The tile by the number of workgroups it gives 256 CUs (measured alone
     // on the encoder's launches of 1 to 32 segments, d = 512, 768 and 1280):
     //  - 64 x 64 while 128 x 128 tiles are fewer than 144 (d = 1280, one
-    //    segment, fc2: 36.8 us against 56.5 with 128, 133.7 with 256);
-    //  - for K <= 640 with at least 750 of them, 256 x 128, two workgroups per
-    //    CU (d = 512, 32 segments, fc1: 150 against 162 and 153 us);
-    //  - for longer K, 256 x 256 where its last round of one per CU leaves less
-    //    than a tenth of the time idle (d = 1280, 8 segments, fc2: 149 against
-    //    165 us with 128);
-    //  - 128 x 128, two per CU, otherwise (5 segments, QK: 61.7 against 82.9 us
-    //    with 256; 16 segments at d = 768, fc2: 132 against 181 us).
+    //    segment, fc2: 36.5 us against 56.4 with 128, 102.7 with 256);
+    //  - 256 x 256, one per CU, if they fit one round and fill at least 144
+    //    CUs (d = 1280, 5 segments, fc2, 150 tiles: 106 against 130 us with
+    //    128; 4 segments, 120 tiles: 105 against 84), or if their rounds are
+    //    at least 75 % full (70 % for K >= 2048, where they gain most; d = 768,
+    //    32 segments, 73 % full: fc2 268 against 306 us, V 77.6 against 75.6);
+    //  - for K <= 640 with at least 750 of them, 256 x 128, two per CU (d = 512,
+    //    16 segments, QK: 38.5 against 41.7 us with 128);
+    //  - 128 x 128, two per CU, otherwise.
     // WHISPER_GEMM_TILE = 64, 128, 256 or 384 (256 x 128) forces one.
     static const int force = [] {
         const char* g = getenv("WHISPER_GEMM_TILE");
@@ -440,10 +530,8 @@ inline void gemm_bf16(const bf16* A, int lda, long long sA, const bf16* B, int l
     const long long t128 = (long long)((MA + 127) / 128) * ((MB + 127) / 128) * batch;
     const long long t384 = (long long)tilesA * ((MB + gh::BN - 1) / gh::BN) * batch;
     const long long t256 = (long long)tilesA * tilesB * batch;
-    const int tile = force ? force
-                   : t128 < 144 ? 64
-                   : K <= 640 ? (t384 >= 750 ? 384 : 128)
-                   : t256 * 10 >= (t256 + 255) / 256 * 256 * 9 ? 256 : 128;
+    const bool big = t256 <= 256 ? t256 >= 144 : t256 * 100 >= (t256 + 255) / 256 * 256 * (K >= 2048 ? 70 : 75);
+    const int tile = force ? force : t128 < 144 ? 64 : big ? 256 : K <= 640 && t384 >= 750 ? 384 : 128;
     if (tile == 64) return gemm_tile<bf16, 2, 4>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
     if (tile == 128) return gemm_tile<bf16, 4, 2>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
     if (tile == 384) {
