@@ -8,7 +8,8 @@
 //   H1pad [nb][3002][d]     first conv output, row 1 + t, zero row 0
 //   x     [nb * 1500][d]    fp32 residual stream
 //   Qh,Kh [nb][H][TQ][64]   per-head queries (scaled by log2(e)/8) and keys
-//   Vt    [nb][H][64][TQ]   per-head values, transposed
+//   Vt    [nb][H][64][TQ]   per-head values, transposed; in bf16 the positions
+//                           of a row are ordered by vt_pos
 // Decoder caches (slot s, layer l, head h):
 //   self  Kt [l][s][h][64][TS], V [l][s][h][TS][64]
 //   cross Kt [l][s][h][64][TC], V [l][s][h][TC][64]
@@ -87,6 +88,17 @@ struct EpiQK {  // A = [Wq; Wk] (2d rows), B = tokens
     }
 };
 
+// Where position t of a V^T row is stored. The bf16 attention's P V MFMA
+// reduces over 32 keys, of which lane group g takes keys 4 g .. + 3 and
+// 16 + 4 g .. + 3 (those whose scores it holds); they are stored side by side,
+// so a V^T fragment is one 16-byte read. Four positions from a multiple of
+// four stay consecutive.
+template <class T>
+__host__ __device__ inline int vt_pos(int t) {
+    if constexpr (sizeof(T) == 2) return (t & ~31) | ((t & 12) << 1) | ((t & 16) >> 2) | (t & 3);
+    else return t;
+}
+
 template <class T>
 struct EpiVt {  // A = tokens (4 consecutive positions), B = Wv
     const float* bv;
@@ -97,7 +109,7 @@ struct EpiVt {  // A = tokens (4 consecutive positions), B = Wv
         const int bseg = m / N_CTX, t = m - bseg * N_CTX;
         const int h = f >> 6, jj = f & 63;
         const float bb = p.a.x;
-        st4(vt + (((long long)bseg * H + h) * 64 + jj) * TQ + t, a + bb, b + bb, c + bb, e + bb);
+        st4(vt + (((long long)bseg * H + h) * 64 + jj) * TQ + vt_pos<T>(t), a + bb, b + bb, c + bb, e + bb);
     }
 };
 

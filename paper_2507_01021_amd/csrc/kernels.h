@@ -411,20 +411,21 @@ __global__ __launch_bounds__(resid_ln_threads<E>()) void resid_ln_kernel(const f
 //
 // Non-causal attention of every query over all 1500 keys, per (segment,
 // head). Q, K: [BH][TQ][64] (Q scaled by 1/8), Vt: [BH][64][TQ].
-// Workgroup: 4 waves x 64 queries; key tiles of 64 staged in LDS (double
-// buffer). Per wave and key tile:
+// Workgroup: 4 waves x 64 queries; key tiles of 64 in LDS (two buffers filled
+// by direct global->LDS loads, one barrier per tile). Per wave and key tile:
 //   S^T[key][q] = K Q^T          (A = K rows from LDS, B = Q in registers)
 //   online softmax per query      (each lane owns one query per 16-block)
 //   O^T[dim][q] += V^T P^T        (A = V^T from LDS, B = P from registers)
 // The P operand uses the lane's own S values directly: the MFMA's reduction
 // index k is mapped to keys so that lane l's eight k's are the keys it holds
-// (keys 4*(l/16)+{0..3} of two 16-key blocks); V^T is read with the same map.
-// LDS tiles are [64 rows][128 bytes] with 16-byte chunks XOR-swizzled by the
-// row. The V^T fragment reads are 8 bytes per lane, and the 16 lanes of one
-// LDS pass read rows r..r+15 at the same key offset: with the 16-byte swizzle
-// alone, rows r and r+8 would hit the same chunk half (a 2-way bank conflict
-// on every pass). In the V^T tile the two 8-byte halves of each chunk are
-// therefore swapped in rows whose bit 3 is set.
+// (keys 4*(l/16)+{0..3} of two 16-key blocks); V^T is stored in that order
+// (vt_pos), so K and V^T fragments are 16-byte reads. LDS tiles are [64
+// rows][128 bytes] with 16-byte chunks XOR-swizzled by the row.
+// The tile loop has no exchange between lanes: the sums of weights stay per
+// lane until the end, and a query's maximum is gathered from its four lanes
+// only on the rare tiles that move its reference. 32 segments x 20 heads:
+// about 435 us (845 TFLOP/s); with both exchanges in every tile, K and V staged
+// through registers and V^T read in halves of 8 bytes about 500 us.
 namespace ea {
 constexpr int QW = 64;             // queries per wave
 constexpr int QB = 4 * QW;         // queries per workgroup
@@ -469,33 +470,25 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
         lrun[u] = 0.f;
         negm[u] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    // staging: thread copies 16-byte chunk (tid & 7) of rows (tid >> 3) and +32
-    const int lc = tid & 7, lr = tid >> 3;
-    u32x4 rk[2], rv[2];
-    auto gload = [&](int k0) {
+    // direct loads: wave w fills rows 16 w .. 16 w + 15 of both tiles, 8 rows
+    // per instruction; lane i loads the logical chunk stored at position i % 8
+    const int sr = lane >> 3, sc = (lane & 7) ^ sr;
+    const bf16* kp = Kb + (wave * 16 + sr) * 64 + sc * 8;
+    const bf16* vp = Vb + (long long)(wave * 16 + sr) * TQ + sc * 8;
+    auto issue = [&](int kt) {
+        unsigned char* tk = lds + (kt & 1) * 2 * ea::TILE + wave * 2048;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            rk[s] = *reinterpret_cast<const u32x4*>(Kb + (long long)(k0 + lr + 32 * s) * 64 + lc * 8);
-            rv[s] = *reinterpret_cast<const u32x4*>(Vb + (long long)(lr + 32 * s) * TQ + k0 + lc * 8);
+            __builtin_amdgcn_global_load_lds(kp + (kt * ea::KT + 8 * s) * 64, tk + s * 1024, 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(vp + 8 * s * TQ + kt * ea::KT, tk + ea::TILE + s * 1024, 16, 0, 0);
         }
     };
-    const bool vswap = (lr >> 3) & 1;  // bit 3 of this thread's rows lr and lr + 32
-    auto lstore = [&](int buf) {
-        unsigned char* tk = lds + buf * 2 * ea::TILE;
-        unsigned char* tv = tk + ea::TILE;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            *reinterpret_cast<u32x4*>(tk + swz(lr + 32 * s, lc)) = rk[s];
-            *reinterpret_cast<u32x4*>(tv + swz(lr + 32 * s, lc)) =
-                vswap ? u32x4{rv[s].z, rv[s].w, rv[s].x, rv[s].y} : rv[s];
-        }
-    };
-    const int ntiles = (N_CTX + ea::KT - 1) / ea::KT;
-    gload(0);
-    lstore(0);
-    __syncthreads();
+    constexpr int ntiles = (N_CTX + ea::KT - 1) / ea::KT;
+    issue(0);
     for (int kt = 0; kt < ntiles; ++kt) {
-        if (kt + 1 < ntiles) gload((kt + 1) * ea::KT);
+        __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
+        __builtin_amdgcn_s_barrier();  // tile kt is in LDS and every wave is done with tile kt - 1
+        if (kt + 1 < ntiles) issue(kt + 1);
         const unsigned char* tk = lds + (kt & 1) * 2 * ea::TILE;
         const unsigned char* tv = tk + ea::TILE;
         // K fragments (A operand of S^T = K Q^T): key a*16 + fr, dims s*32 + fc*8 .. +7
@@ -536,12 +529,12 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
             for (int a = 0; a < 4; ++a)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) mx = fmaxf(mx, scur[a][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
             // The first tile sets mref to its maximum; later tiles move it
             // only when their maximum is more than 8 above it, and then scale
             // the sums so far by 2^-(the move).
             if (kt == 0 || __any(mx > 8.f)) {
+                mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
                 const float delta = (kt == 0 || mx > 8.f) ? mx : 0.f;
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
@@ -568,9 +561,7 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
                     pv[a][r] = exp2_softmax(scur[a][r]);
                     ls += pv[a][r];
                 }
-            ls += __shfl_xor(ls, 16, 64);
-            ls += __shfl_xor(ls, 32, 64);
-            lrun[u] += ls;
+            lrun[u] += ls;  // this lane's keys
             // P operand for key half s: keys s*32 + fc*4 + {0..3} and s*32 + 16 + fc*4 + {0..3}
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
@@ -591,22 +582,17 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 // V^T row (dim) a*16 + fr, keys s*32 + fc*4 .. +3 and s*32 + 16 + fc*4 .. +3
-                // (bit 3 of the row is bit 3 of fr; it selects the swapped halves)
-                const int row = a * 16 + fr, half = (fr >> 3) & 1;
-                const int kA = s * 32 + fc * 4, kB = kA + 16;
-                const u32x2 lo =
-                    *reinterpret_cast<const u32x2*>(tv + swz(row, kA >> 3) + ((((kA & 7) >> 2) ^ half) << 3));
-                const u32x2 hi =
-                    *reinterpret_cast<const u32x2*>(tv + swz(row, kB >> 3) + ((((kB & 7) >> 2) ^ half) << 3));
-                union { u32x4 u; mfma_bf16x8 v; } cvt;
-                cvt.u = u32x4{lo.x, lo.y, hi.x, hi.y};
+                const mfma_bf16x8 vf = *reinterpret_cast<const mfma_bf16x8*>(tv + swz(a * 16 + fr, 4 * s + fc));
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    o[a][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cvt.v, pf[u][s], o[a][u], 0, 0, 0);
+                    o[a][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[u][s], o[a][u], 0, 0, 0);
             }
         }
-        if (kt + 1 < ntiles) lstore((kt + 1) & 1);
-        __syncthreads();
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        lrun[u] += __shfl_xor(lrun[u], 16, 64);
+        lrun[u] += __shfl_xor(lrun[u], 32, 64);
     }
     // lane holds O^T[dim a*16 + fc*4 + r][query q0 + u*16 + fr]
 #pragma unroll
