@@ -1,8 +1,8 @@
 // Non-GEMM kernels of the batched Whisper path on gfx950: audio framing
 // buffer, log-mel normalisation, layer norm, decoder embedding, encoder
-// attention (bf16 MFMA flash attention; fp32 SIMT variant), decode-step
-// attention over the KV caches, the skinny decode GEMM (bf16 MFMA streaming
-// each weight once) and the greedy argmax step.
+// attention (bf16 and fp32 MFMA flash attention), decode-step attention over
+// the KV caches, the skinny decode GEMM (MFMA, streaming each weight once) and
+// the greedy argmax step.
 #pragma once
 
 #include "common.h"
