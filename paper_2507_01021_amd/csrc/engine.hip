@@ -248,7 +248,7 @@ __global__ void probe_wait_kernel(int* flag, int* seen) {
         f = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_s_sleep(8);
     }
-    *seen = f;
+    __hip_atomic_store(seen, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __global__ void probe_set_kernel(int* flag, int v) {
     __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -299,8 +299,10 @@ class EngineT final : public Engine {
         if (std::is_same<T, bf16>::value) n_side_ = std::max(ctc_ ? 1 : chains_, enc_parts_) - 1;
         for (int c = 1; c <= n_side_; ++c) WMI_HIP(hipEventCreateWithFlags(&join_ev_[c], hipEventDisableTiming));
         WMI_HIP(hipEventCreateWithFlags(&fork_ev_, hipEventDisableTiming));
-        probe_ = dalloc<int>(2);
+        probe_ = dalloc<int>(1);
+        WMI_HIP(hipHostMalloc(reinterpret_cast<void**>(&probe_seen_), sizeof(int)));
         choose_side_streams();
+        side_picked_ = true;
         load_weights(blob, bytes);
         alloc_state();
         scratch_ = static_cast<unsigned char*>(scratch_address(dev_));
@@ -331,6 +333,7 @@ class EngineT final : public Engine {
             if (stop_ev_[b]) (void)hipEventDestroy(stop_ev_[b]);
         }
         for (void* q : allocs_) (void)hipFree(q);
+        if (probe_seen_) (void)hipHostFree(probe_seen_);
         if (fork_ev_) (void)hipEventDestroy(fork_ev_);
         for (int c = 1; c < MAXC; ++c)
             if (join_ev_[c]) (void)hipEventDestroy(join_ev_[c]);
@@ -346,27 +349,30 @@ class EngineT final : public Engine {
     void set_stream(void* s) override {
         join_chains();
         WMI_HIP(hipStreamSynchronize(st_));
-        st_ = s ? static_cast<hipStream_t>(s) : own_stream_;
+        const hipStream_t next = s ? static_cast<hipStream_t>(s) : own_stream_;
+        if (next == st_ && side_picked_) return;
+        st_ = next;
+        side_picked_ = false;
         // never waits for the caller's stream: one that is busy or being
         // captured keeps the side streams as they are
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st_, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-            hipStreamQuery(st_) == hipSuccess)
+            hipStreamQuery(st_) == hipSuccess) {
             choose_side_streams();
+            side_picked_ = true;
+        }
         (void)hipGetLastError();  // "not ready" is no error here
     }
 
     // Whether stream b runs beside stream a (see probe_wait_kernel).
     bool overlaps(hipStream_t a, hipStream_t b) {
-        int seen = 0;
         hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, b, probe_, 0);  // also b's first use
         WMI_HIP(hipStreamSynchronize(b));
-        hipLaunchKernelGGL(probe_wait_kernel, dim3(1), dim3(1), 0, a, probe_, probe_ + 1);
+        hipLaunchKernelGGL(probe_wait_kernel, dim3(1), dim3(1), 0, a, probe_, probe_seen_);
         hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, b, probe_, 1);
         WMI_HIP(hipStreamSynchronize(a));
         WMI_HIP(hipStreamSynchronize(b));
-        WMI_HIP(hipMemcpy(&seen, probe_ + 1, sizeof(int), hipMemcpyDeviceToHost));
-        return seen != 0;
+        return *probe_seen_ != 0;
     }
 
     // Picks the side streams cst_[1 .. n_side_] for the context's stream: for
@@ -1102,8 +1108,11 @@ class EngineT final : public Engine {
     // side streams: decode chains 1.. and parts 1.. of an encoder pass (chain and part 0: st_)
     hipStream_t cst_[MAXC] = {};
     int n_side_ = 0;
+    bool side_picked_ = false;            // cst_ was tried out beside st_
     std::vector<hipStream_t> side_pool_;  // every side stream made; cst_ points into it
-    int* probe_ = nullptr;                // flag and answer of overlaps()
+    // flag of overlaps(), and its answer in pinned host memory: a synchronous
+    // copy of it would wait for the program's other streams too
+    int *probe_ = nullptr, *probe_seen_ = nullptr;
     int enc_parts_ = 2;
     hipEvent_t fork_ev_ = nullptr, join_ev_[MAXC] = {};
     // host staging
