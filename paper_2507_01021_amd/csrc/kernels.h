@@ -421,17 +421,32 @@ __global__ __launch_bounds__(resid_ln_threads<E>()) void resid_ln_kernel(const f
 // (keys 4*(l/16)+{0..3} of two 16-key blocks); V^T is stored in that order
 // (vt_pos), so K and V^T fragments are 16-byte reads. LDS tiles are [64
 // rows][128 bytes] with 16-byte chunks XOR-swizzled by the row.
-// The tile loop has no exchange between lanes: the sums of weights stay per
-// lane until the end, and a query's maximum is gathered from its four lanes
-// only on the rare tiles that move its reference. 32 segments x 20 heads:
-// about 435 us (845 TFLOP/s); with both exchanges in every tile, K and V staged
-// through registers and V^T read in halves of 8 bytes about 500 us.
+// A query's maximum is gathered from its four lanes only on the rare tiles
+// that move its reference. Its weights are added over the four lanes in every
+// tile, tile after tile (the order fixes the bits of every layer that
+// follows); group_sums does so for the wave's four query tiles with three lane
+// swaps and leaves each in the lane group of its number. 32 segments x 20
+// heads: 412-427 us (about 870 TFLOP/s); with the sums left per lane until
+// the end 403-427 us, with lane exchanges through LDS in every tile, K and V
+// staged through registers and V^T read in halves of 8 bytes 444-450 us.
 namespace ea {
 constexpr int QW = 64;             // queries per wave
 constexpr int QB = 4 * QW;         // queries per workgroup
 constexpr int KT = 64;             // keys per tile
 constexpr int TILE = KT * 64 * 2;  // bytes of one K or V^T tile
 }  // namespace ea
+
+// Sums of v[u] over the four lanes l % 16 + 16 g, ((g0 + g1) + (g2 + g3)),
+// left in lane group u: three lane swaps for all four sums.
+__device__ inline float group_sums(const float (&v)[4]) {
+    auto swap16 = [](float a, float b) {  // groups (a0 + a1, b0 + b1, a2 + a3, b2 + b3)
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    const float x = swap16(v[0], v[1]), y = swap16(v[2], v[3]);
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
 __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                                const bf16* __restrict__ Vt, bf16* __restrict__ O,
@@ -462,12 +477,11 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
     // query keeps a reference mref (a score it has seen, at most 8 below its
     // running maximum) and the score MFMAs start from -mref, so they return
     // s - mref and the weights are plain exp2 of the result, at most 2^8.
-    float mref[4], lrun[4];
+    float mref[4], lrun = 0.f;  // lane group fc: query tile fc's sum of weights
     mfma_f32x4 negm[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         mref[u] = 0.f;
-        lrun[u] = 0.f;
         negm[u] = mfma_f32x4{0.f, 0.f, 0.f, 0.f};
     }
     // direct loads: wave w fills rows 16 w .. 16 w + 15 of both tiles, 8 rows
@@ -521,6 +535,7 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
         // and the matrix cores work at the same time.
         mfma_f32x4 scur[4], snext[4];
         mfma_bf16x8 pf[4][2];
+        float lt[4];
         scores(0, scur);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -544,7 +559,7 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
                 negm[u] = mfma_f32x4{-mref[u], -mref[u], -mref[u], -mref[u]};
                 if (kt > 0) {
                     const float alpha = exp2_softmax(-delta);
-                    lrun[u] *= alpha;
+                    lrun *= fc == u ? alpha : 1.f;
 #pragma unroll
                     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -561,7 +576,7 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
                     pv[a][r] = exp2_softmax(scur[a][r]);
                     ls += pv[a][r];
                 }
-            lrun[u] += ls;  // this lane's keys
+            lt[u] = ls;  // this lane's keys
             // P operand for key half s: keys s*32 + fc*4 + {0..3} and s*32 + 16 + fc*4 + {0..3}
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
@@ -576,6 +591,7 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
 #pragma unroll
             for (int a = 0; a < 4; ++a) scur[a] = snext[a];
         }
+        lrun += group_sums(lt);
         // O^T += V^T P^T
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -589,17 +605,13 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
             }
         }
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        lrun[u] += __shfl_xor(lrun[u], 16, 64);
-        lrun[u] += __shfl_xor(lrun[u], 32, 64);
-    }
     // lane holds O^T[dim a*16 + fc*4 + r][query q0 + u*16 + fr]
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
+        const float lu = __shfl(lrun, u * 16 + fr, 64);
         const int q = q0 + u * 16 + fr;
         if (q >= N_CTX) continue;
-        const float inv = 1.0f / lrun[u];
+        const float inv = 1.0f / lu;
         bf16* orow = O + ((long long)bseg * N_CTX + q) * d + h * 64;
 #pragma unroll
         for (int a = 0; a < 4; ++a)
