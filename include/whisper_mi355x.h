@@ -455,6 +455,24 @@ whisper_status whisper_test_batcher(int32_t n, const int64_t* arrival_us, const 
 whisper_status whisper_test_greedy_keys(const float* logits, int32_t rows, int32_t n_vocab,
                                         const uint32_t* excluded, int32_t* tokens, int32_t* no_token);
 
+/* Kernel variants whose choice by sizes whisper_test_kernel_choice reports. */
+typedef enum {
+    /* decoder projection; sizes: output features, split-K parts, rows, waves that share a reduction
+       (4, or 8: the residual projection of bf16 models); choice: 1 = the kernel for many rows */
+    WHISPER_CHOICE_DEC_PROJ = 0,
+    WHISPER_CHOICE_COUNT = 1
+} whisper_choice;
+
+/*
+ * Host-only check of the engine's dispatch (no device work): the variant
+ * that a launch of the given sizes takes in a model of type `dtype`
+ * (whisper_dtype). sizes: host array of n_sizes values as listed at
+ * `choice_of` (whisper_choice); *choice receives the variant. Errors:
+ * WHISPER_E_INVAL.
+ */
+whisper_status whisper_test_kernel_choice(int32_t choice_of, int32_t dtype, const int64_t* sizes,
+                                          int32_t n_sizes, int32_t* choice);
+
 #ifdef __cplusplus
 }
 #endif

@@ -18,6 +18,7 @@ DTYPE_F32, DTYPE_BF16 = 0, 1
 T_MEL, T_ENC_OUT, T_CROSS_K, T_CROSS_V, T_CTC_LOGITS, T_CTC_IDS = 0, 1, 2, 3, 4, 5
 K_CROSS_ATTN, K_ENC_GEMM, K_SELF_ATTN, K_ENC_ATTN, K_ENC_PASS, K_DEC_STEP, K_FRONT_END = 0, 1, 2, 3, 4, 5, 6
 K_CROSS_ATTN_STEP = 7
+CHOICE_DEC_PROJ = 0
 
 EXPORTS = (
     "whisper_params_from_blob", "whisper_ctx_create", "whisper_ctx_destroy", "whisper_last_error",
@@ -26,6 +27,7 @@ EXPORTS = (
     "whisper_slot_tokens", "whisper_batch_transcribe", "whisper_batch_serve", "whisper_debug_copy",
     "whisper_profile_enable", "whisper_profile_read", "whisper_time_kernel", "whisper_stats_read",
     "whisper_set_decoding", "whisper_test_batcher", "whisper_test_greedy_keys",
+    "whisper_test_kernel_choice",
 )
 
 
@@ -93,6 +95,7 @@ def load(path: str = LIB_PATH) -> C.CDLL:
                                       pi32, i64, C.POINTER(whisper_result), pi32, i32, pi32, i32, i64, i64, i32,
                                       i32, i64, i64]),
         "whisper_test_greedy_keys": (i32, [C.POINTER(C.c_float), i32, i32, C.POINTER(C.c_uint32), pi32, pi32]),
+        "whisper_test_kernel_choice": (i32, [i32, i32, C.POINTER(i64), i32, pi32]),
     }
     for name, (res, args) in sig.items():
         f = getattr(lib, name)
@@ -321,3 +324,11 @@ def test_greedy_keys(logits, excluded_ids=()):
                                         None if mask is None else _ptr(mask, C.c_uint32),
                                         _ptr(tok, C.c_int32), _ptr(bad, C.c_int32)))
     return tok[:rows], bad[:rows]
+
+
+def test_kernel_choice(choice_of, dtype, *sizes) -> int:
+    """The kernel variant that a launch of the given sizes takes (host only)."""
+    a = np.asarray(sizes, dtype=np.int64)
+    out = C.c_int32()
+    _check(load().whisper_test_kernel_choice(choice_of, dtype, _ptr(a, C.c_int64), a.size, C.byref(out)))
+    return out.value

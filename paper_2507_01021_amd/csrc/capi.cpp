@@ -759,4 +759,13 @@ whisper_status whisper_test_greedy_keys(const float* logits, int32_t rows, int32
     return WHISPER_OK;
 }
 
+whisper_status whisper_test_kernel_choice(int32_t choice_of, int32_t dtype, const int64_t* sizes,
+                                          int32_t n_sizes, int32_t* choice) {
+    int c = 0;
+    if (!sizes || n_sizes < 1 || !choice || !wmi::kernel_choice(choice_of, dtype, sizes, n_sizes, &c))
+        return fail(nullptr, WHISPER_E_INVAL, "bad arguments");
+    *choice = c;
+    return WHISPER_OK;
+}
+
 }  // extern "C"

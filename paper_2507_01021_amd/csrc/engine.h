@@ -90,6 +90,10 @@ std::unique_ptr<Engine> make_engine(const whisper_params& p, const void* blob, s
 // ties, excluded ids skipped, token 0 and bad[r] = 1 for a row with none).
 void greedy_keys_host(const float* logits, int rows, int V, const unsigned* excluded, int* tokens, int* bad);
 
+// The kernel variant that a launch of these sizes takes (whisper_choice);
+// false if the arguments are not those of the choice.
+bool kernel_choice(int choice_of, int dtype, const int64_t* sizes, int n_sizes, int* choice);
+
 // Blob header check; fills the model fields of *out. Returns a whisper_status.
 int parse_blob_header(const void* blob, size_t bytes, whisper_params* out, const char** why);
 

@@ -1627,6 +1627,21 @@ void greedy_keys_host(const float* logits, int rows, int V, const unsigned* excl
     }
 }
 
+bool kernel_choice(int choice_of, int dtype, const int64_t* sizes, int n_sizes, int* choice) {
+    if (dtype != WHISPER_DTYPE_F32 && dtype != WHISPER_DTYPE_BF16) return false;
+    const bool f32 = dtype == WHISPER_DTYPE_F32;
+    for (int i = 0; i < n_sizes; ++i)
+        if (sizes[i] < 1 || sizes[i] > INT32_MAX) return false;
+    if (choice_of == WHISPER_CHOICE_DEC_PROJ) {
+        if (n_sizes != 4 || (sizes[3] != 4 && sizes[3] != RESID_NW) || (f32 && sizes[3] != 4)) return false;
+        const int MA = (int)sizes[0], KS = (int)sizes[1], n = (int)sizes[2];
+        *choice = f32 ? many_rows<float, 4>(MA, KS, n)
+                : sizes[3] == 4 ? many_rows<bf16, 4>(MA, KS, n) : many_rows<bf16, RESID_NW>(MA, KS, n);
+        return true;
+    }
+    return false;
+}
+
 std::unique_ptr<Engine> make_engine(const whisper_params& p, const void* blob, size_t bytes, int device) {
     if (p.dtype == WHISPER_DTYPE_BF16) return std::unique_ptr<Engine>(new EngineT<bf16>(p, blob, bytes, device));
     return std::unique_ptr<Engine>(new EngineT<float>(p, blob, bytes, device));

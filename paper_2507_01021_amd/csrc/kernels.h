@@ -1783,9 +1783,23 @@ __global__ __launch_bounds__(256) void many_kernel(const T* __restrict__ W, cons
             epi((tile + t) * 16 + fc * 4, r, blockIdx.y, tot[t][u][0], tot[t][u][1], tot[t][u][2], tot[t][u][3], pre[t]);
     }
 }
-// Worth it once its workgroups (128 weight rows x 64 rows) reach half the
-// CUs; below that the one-tile workgroups spread better.
-inline bool many_rows(int MA, int KS, int groups) { return MA % 128 == 0 && MA / 128 * KS * groups >= 128; }
+// A wave of many_kernel runs the whole reduction of its tile alone, so a
+// launch takes about as long with one workgroup as with one on every CU, and
+// skinny_kernel's many short waves are faster until then. Measured (us,
+// skinny / many): d = 2048, fc2 (KS = 8), 1 row 8.3 / 24.1, 64 rows (128
+// workgroups) 16.9 / 25.6, 96 rows (256) 26.4 / 25.2; d = 1280, QKV, 384 rows
+// (180) 18.8 / 23.2, 512 rows (240) 24.3 / 23.3; d = 512, fc1, 1024 rows (256)
+// 1.06 times skinny's. With 8 sequences (skinny_resid) it is worth it from 192
+// workgroups (d = 1536, 1024 rows: 28.5 / 27.5; d = 1280, 1024 rows, 160: 23.0
+// / 27.7), in fp32, where its MFMAs take longer, from 384 (d = 2048, fc1, 256
+// rows, 256 workgroups 1.24 times skinny's, 384 rows, 384 workgroups 0.96
+// times). No launch of up to 64 rows has that many.
+template <class T, int NW>
+constexpr int MANY_WGS = sizeof(T) == 4 ? 384 : NW == 8 ? 192 : 256;
+template <class T, int NW>
+inline bool many_rows(int MA, int KS, int n) {
+    return MA % 128 == 0 && (long long)(MA / 128) * KS * ((n + 63) / 64) >= MANY_WGS<T, NW>;
+}
 
 // skinny_kernel for up to 16 rows whose activations are a split
 // cross-attention's chunk results: a lane merges its fragment's elements
@@ -1894,7 +1908,7 @@ inline void skinny_resid(const bf16* W, int d, const bf16* X, int n, int K, cons
     if (K % 32 || n <= 0 || d % 32) throw ArgError(-1, "skinny_resid: unsupported shape");
     const int nks = K / 32, groups = (n + 63) / 64;
     const EpiResidX epi{bias, x, d};
-    if (many_rows(d, 1, groups)) {
+    if (many_rows<bf16, RESID_NW>(d, 1, n)) {
         hipLaunchKernelGGL((many_kernel<bf16, RESID_NW, EpiResidX>), dim3(d / 128, 1, groups), dim3(256), 0, st, W, X, nks,
                            n, K, epi);
         return;
@@ -1932,7 +1946,7 @@ template <class T, class Epi>
 inline void skinny(const T* W, int MA, const T* X, int n, int K, int KS, const Epi& epi, hipStream_t st) {
     if (KS < 1 || K % (KSTEP<T> * KS) || n <= 0 || MA <= 0) throw ArgError(-1, "skinny: unsupported shape");
     const int Kc = K / KS, nks_tot = K / KSTEP<T>, groups = (n + 63) / 64;
-    if (many_rows(MA, KS, groups)) {
+    if (many_rows<T, 4>(MA, KS, n)) {
         hipLaunchKernelGGL((many_kernel<T, 4, Epi>), dim3(MA / 128, KS, groups), dim3(256), 0, st, W, X, nks_tot, n, Kc,
                            epi);
         return;

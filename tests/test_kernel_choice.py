@@ -1,0 +1,53 @@
+"""The engine's dispatch rules on the host: which kernel variant a launch of
+given sizes takes."""
+import os
+
+import pytest
+
+from paper_2507_01021_amd import binding
+from paper_2507_01021_amd.binding import DTYPE_BF16, DTYPE_F32
+
+WIDTHS = [384, 512, 768, 1024, 1280, 1536, 2048]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    if not os.path.exists(binding.LIB_PATH):
+        pytest.skip("library not built (python -m paper_2507_01021_amd.build)")
+    return binding.load()
+
+
+def projections(d):
+    """(output features, split-K parts, waves) of a decoder layer's projections."""
+    return [(3 * d, 1, 4), (d, 4, 4), (d, 1, 8), (d, 1, 4), (4 * d, 1, 4), (d, 8, 4)]
+
+
+def many(dtype, MA, KS, n, NW):
+    return binding.test_kernel_choice(binding.CHOICE_DEC_PROJ, dtype, MA, KS, n, NW)
+
+
+@pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
+def test_steps_of_few_rows_keep_the_skinny_kernel(dtype):
+    for d in WIDTHS:
+        for MA, KS, NW in projections(d):
+            if NW == 8 and dtype == DTYPE_F32:
+                continue
+            for n in (1, 16, 17, 64):
+                assert many(dtype, MA, KS, n, NW) == 0, (d, MA, KS, n, NW)
+
+
+def test_prefill_chunks_take_the_kernel_for_many_rows():
+    # 2048 rows: every projection from d = 768 on; 1520 rows: all but the residual projection
+    for MA, KS, NW in projections(768):
+        if (MA, KS, NW) == (768, 1, 4):
+            continue  # 192 workgroups of a short reduction
+        assert many(DTYPE_BF16, MA, KS, 2048, NW) == 1, (MA, KS, NW)
+        assert many(DTYPE_BF16, MA, KS, 1520, NW) == (NW == 4), (MA, KS, NW)
+
+
+def test_bad_choice_arguments_are_refused():
+    for args in [(binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 0, 4), (binding.CHOICE_DEC_PROJ, DTYPE_F32, 1280, 1, 1, 8),
+                 (binding.CHOICE_DEC_PROJ, 2, 1280, 1, 1, 4), (binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 1), (99, 0, 1)]:
+        with pytest.raises(binding.WhisperError) as e:
+            binding.test_kernel_choice(*args)
+        assert e.value.status == binding.E_INVAL
