@@ -460,7 +460,10 @@ typedef enum {
     /* decoder projection; sizes: output features, split-K parts, rows, waves that share a reduction
        (4, or 8: the residual projection of bf16 models); choice: 1 = the kernel for many rows */
     WHISPER_CHOICE_DEC_PROJ = 0,
-    WHISPER_CHOICE_COUNT = 1
+    /* cross-attention of prefill rows; sizes: rows, heads, groups (up to 8 rows of one slot each);
+       choice: 1 = a workgroup per group, 0 = a workgroup per row */
+    WHISPER_CHOICE_PREFILL_CROSS = 1,
+    WHISPER_CHOICE_COUNT = 2
 } whisper_choice;
 
 /*

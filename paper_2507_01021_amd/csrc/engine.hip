@@ -587,7 +587,7 @@ class EngineT final : public Engine {
             prof_begin(WHISPER_K_CROSS_ATTN, s);
             const bool split = n <= b.xrows && cross_split(n);
             const CrossPart cp{b.xpart, reinterpret_cast<float2*>(b.xpart + (size_t)n * H_ * CW * 64)};
-            if (b.groups)
+            if (b.groups && share_rows<T>(n, H_, b.ngroups))
                 hipLaunchKernelGGL(cross_attn_rows_kernel<T>, dim3(H_, b.ngroups), dim3(64 * CW), 0, s, ca, b.groups);
             else if (split)
                 hipLaunchKernelGGL(cross_attn_split_kernel<T>, dim3(H_, n, CW), dim3(128), 0, s, ca, cp);
@@ -1637,6 +1637,12 @@ bool kernel_choice(int choice_of, int dtype, const int64_t* sizes, int n_sizes, 
         const int MA = (int)sizes[0], KS = (int)sizes[1], n = (int)sizes[2];
         *choice = f32 ? many_rows<float, 4>(MA, KS, n)
                 : sizes[3] == 4 ? many_rows<bf16, 4>(MA, KS, n) : many_rows<bf16, RESID_NW>(MA, KS, n);
+        return true;
+    }
+    if (choice_of == WHISPER_CHOICE_PREFILL_CROSS) {
+        if (n_sizes != 3) return false;
+        const int n = (int)sizes[0], H = (int)sizes[1], g = (int)sizes[2];
+        *choice = f32 ? share_rows<float>(n, H, g) : share_rows<bf16>(n, H, g);
         return true;
     }
     return false;

@@ -1374,6 +1374,22 @@ __global__ __launch_bounds__(64 * CW) void cross_attn_rows_kernel(DecAttnArgs a,
     }
 }
 
+// Whether n prefill rows in `groups` groups share their slots' keys and values
+// (cross_attn_rows_kernel) or run one per workgroup (cross_attn_kernel). A
+// group takes a CU about 30 us whether it has one row or eight, two on a CU
+// twice that, so its launch takes 30 us per 256 workgroups, the last of them
+// counted whole; a workgroup of one row takes a third of that in bf16 (768
+// fill the same time) and about all of it in fp32. Measured (us, one row /
+// shared), 12 heads: 4 slots of 1 row 11.6 / 30.0, 16 slots of 3 rows (576
+// workgroups of one row) 32.4 / 32.2, of 5 rows (960) 46.9 / 32.4, 32 slots
+// (two rounds) of 2 rows 44.7 / 61.9, of 5 rows (1920) 82.1 / 62.4; fp32, 6
+// heads: 8 slots of 4 rows (192) 29.6 / 29.5, of 6 rows (288) 47.3 / 29.4.
+template <class T>
+inline bool share_rows(int n, int H, int groups) {
+    constexpr int ONE_ROW = sizeof(T) == 2 ? 768 : 256;
+    return (long long)n * H > (long long)ONE_ROW * (((long long)groups * H + 255) / 256);
+}
+
 // Timing slots of n launches: start = all ones (for a minimum), end = 0.
 __global__ void stamp_reset_kernel(unsigned long long* __restrict__ s, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;

@@ -1,9 +1,10 @@
 """Prefill of many rows: the projections' and the cross-attention's variants
 for many rows (many_kernel, skinny_ln_kernel with 32 weight rows,
-cross_attn_rows_kernel) and the boundary between two chunks of 2048 rows,
-which falls inside a slot's prompt. Each of them keeps the order of every sum
-of the one-position step, so the logits after a prefilled prompt equal those
-of the prompt fed one position per step bit for bit."""
+cross_attn_rows_kernel), those that few rows keep, and the boundary between
+two chunks of 2048 rows, which falls inside a slot's prompt. Each of them keeps
+the order of every sum of the one-position step, so the logits after a
+prefilled prompt equal those of the prompt fed one position per step bit for
+bit."""
 import numpy as np
 import pytest
 
@@ -12,6 +13,12 @@ from paper_2507_01021_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 CASES = {
+    # few rows: one workgroup per row
+    "base-short": (synth.BASE, [2, 3, 5, 2]),
+    "tiny-short": (synth.TINY, [2, 3, 5, 2]),
+    # enough of them to share a workgroup in fp32, not in bf16
+    "base-three": (synth.BASE, [4] * 16),
+    "tiny-three": (synth.TINY, [4] * 16),
     # rows: one group, a group edge, a full and a partial 64-row group
     "base-few": (synth.BASE, [2, 9, 10, 66, 130]),
     # 2300 rows: two chunks, the second starting inside a prompt
@@ -30,7 +37,7 @@ def test_prefill_of_many_rows_equals_steps(name):
     W = synth.make_weights(shape, 0)
     blob = synth.pack_blob(W)
     n = len(lens)
-    segs = synth.fixed_batch(shape, [16000 * (3 + 3 * i) for i in range(n)], 1, seed=51)
+    segs = synth.fixed_batch(shape, [min(480000, 16000 * (3 + 3 * i)) for i in range(n)], 1, seed=51)
     rng = np.random.default_rng(5)
     for s, k in zip(segs, lens):
         s.prompt = rng.integers(0, shape.n_vocab, k).tolist()

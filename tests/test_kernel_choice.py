@@ -45,6 +45,32 @@ def test_prefill_chunks_take_the_kernel_for_many_rows():
         assert many(DTYPE_BF16, MA, KS, 1520, NW) == (NW == 4), (MA, KS, NW)
 
 
+def shared(dtype, slots, per_slot, H):
+    groups = slots * ((per_slot + 7) // 8)
+    return binding.test_kernel_choice(binding.CHOICE_PREFILL_CROSS, dtype, slots * per_slot, H, groups)
+
+
+@pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
+def test_short_prompts_keep_one_row_per_workgroup(dtype):
+    """One row per slot (a prompt of two tokens) never pays for eight, and few
+    (row, head) pairs run at once anyway."""
+    for H in (6, 8, 12, 16, 20, 24, 32):
+        for slots in range(1, 129):
+            assert shared(dtype, slots, 1, H) == 0, (H, slots)
+        if dtype == DTYPE_BF16:
+            for slots in range(1, 33):
+                assert shared(dtype, slots, 2, H) == 0, (H, slots)
+            assert shared(dtype, 4, 5, H) == 0, H
+
+
+@pytest.mark.parametrize("dtype", [DTYPE_F32, DTYPE_BF16])
+def test_long_prompts_share_their_slots_rows(dtype):
+    for H in (6, 8, 12, 16, 20, 24, 32):
+        for slots in (1, 4, 16, 32):
+            per = 223 if slots > 1 else 440
+            assert shared(dtype, slots, min(per, 2048 // slots), H) == 1, (H, slots)
+
+
 def test_bad_choice_arguments_are_refused():
     for args in [(binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 0, 4), (binding.CHOICE_DEC_PROJ, DTYPE_F32, 1280, 1, 1, 8),
                  (binding.CHOICE_DEC_PROJ, 2, 1280, 1, 1, 4), (binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 1), (99, 0, 1)]:
