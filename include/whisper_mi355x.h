@@ -211,7 +211,12 @@ const char* whisper_last_error(const whisper_ctx* ctx);
 
 /* Runs the context's work on `hip_stream` (a hipStream_t of the context's
  * device, e.g. torch.cuda.current_stream().cuda_stream) from now on; NULL
- * selects the context's own stream. The stream must outlive its use. */
+ * selects the context's own stream. The stream must outlive its use. Waits
+ * for the work on the stream chosen before; enqueues nothing on `hip_stream`,
+ * which may be busy. Work that is split runs on streams of the context's as
+ * well, ordered with `hip_stream` by events; the first such call on a stream
+ * waits for it and tries out (some 0.1 ms, at most a few ms) which of them run
+ * beside it. */
 whisper_status whisper_ctx_set_stream(whisper_ctx* ctx, void* hip_stream);
 
 /*

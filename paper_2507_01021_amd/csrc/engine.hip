@@ -239,19 +239,22 @@ __global__ void put_list_kernel(RowList l, int* __restrict__ dst) {
 // stream gets depends on every stream made before it, so whether a side
 // stream really runs beside the context's stream is tried out: a kernel on
 // one stream waits, for at most PROBE_TICKS of the 100 MHz real-time counter,
-// for a flag that a kernel launched after it on the other stream sets.
-constexpr unsigned long long PROBE_TICKS = 200000;  // 2 ms: the host's own delays must fit
-__global__ void probe_wait_kernel(int* flag, int* seen) {
+// for a token that a kernel launched after it on the other stream writes.
+// Every trial has a token of its own and every side stream its own flag, so a
+// write that comes too late is not taken for a later trial's and need not be
+// waited for.
+constexpr unsigned long long PROBE_TICKS = 50000;  // 0.5 ms: the host's own delays must fit
+__global__ void probe_wait_kernel(int* flag, int token, int* seen) {
     const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-    int f = 0;
+    bool f = false;
     while (!f && __builtin_amdgcn_s_memrealtime() - t0 < PROBE_TICKS) {
-        f = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        f = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == token;
         __builtin_amdgcn_s_sleep(8);
     }
-    __hip_atomic_store(seen, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(seen, f ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__global__ void probe_set_kernel(int* flag, int v) {
-    __hip_atomic_store(flag, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__global__ void probe_set_kernel(int* flag, int token) {
+    __hip_atomic_store(flag, token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ------------------------------------------------------------------ engine
@@ -297,12 +300,13 @@ class EngineT final : public Engine {
         // The decode chains and the parts of an encoder pass are never in
         // flight together and share the side streams; fp32 models use none.
         if (std::is_same<T, bf16>::value) n_side_ = std::max(ctc_ ? 1 : chains_, enc_parts_) - 1;
-        for (int c = 1; c <= n_side_; ++c) WMI_HIP(hipEventCreateWithFlags(&join_ev_[c], hipEventDisableTiming));
-        WMI_HIP(hipEventCreateWithFlags(&fork_ev_, hipEventDisableTiming));
-        probe_ = dalloc<int>(1);
-        WMI_HIP(hipHostMalloc(reinterpret_cast<void**>(&probe_seen_), sizeof(int)));
-        choose_side_streams();
-        side_picked_ = true;
+        if (n_side_ > 0) {
+            for (int c = 1; c <= n_side_; ++c) WMI_HIP(hipEventCreateWithFlags(&join_ev_[c], hipEventDisableTiming));
+            WMI_HIP(hipEventCreateWithFlags(&fork_ev_, hipEventDisableTiming));
+            probe_ = dalloc<int>(POOL);
+            WMI_HIP(hipHostMalloc(reinterpret_cast<void**>(&probe_seen_), sizeof(int)));
+            pick_side_streams();
+        }
         load_weights(blob, bytes);
         alloc_state();
         scratch_ = static_cast<unsigned char*>(scratch_address(dev_));
@@ -349,58 +353,79 @@ class EngineT final : public Engine {
     void set_stream(void* s) override {
         join_chains();
         WMI_HIP(hipStreamSynchronize(st_));
-        const hipStream_t next = s ? static_cast<hipStream_t>(s) : own_stream_;
-        if (next == st_ && side_picked_) return;
-        st_ = next;
-        side_picked_ = false;
-        // never waits for the caller's stream: one that is busy or being
-        // captured keeps the side streams as they are
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st_, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-            hipStreamQuery(st_) == hipSuccess) {
-            choose_side_streams();
-            side_picked_ = true;
-        }
-        (void)hipGetLastError();  // "not ready" is no error here
+        st_ = s ? static_cast<hipStream_t>(s) : own_stream_;
+        // the side streams known to run beside it, or else the present ones
+        // until the first call that splits its work
+        sides_known_ = n_side_ == 0;
+        for (auto& k : known_sides_)
+            if (k.first == st_) use_sides(k.second);
     }
 
-    // Whether stream b runs beside stream a (see probe_wait_kernel).
-    bool overlaps(hipStream_t a, hipStream_t b) {
-        hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, b, probe_, 0);  // also b's first use
-        WMI_HIP(hipStreamSynchronize(b));
-        hipLaunchKernelGGL(probe_wait_kernel, dim3(1), dim3(1), 0, a, probe_, probe_seen_);
-        hipLaunchKernelGGL(probe_set_kernel, dim3(1), dim3(1), 0, b, probe_, 1);
+    typedef std::array<hipStream_t, 4> Sides;  // [1 .. n_side_] used
+    void use_sides(const Sides& q) {
+        for (int c = 1; c <= n_side_; ++c) cst_[c] = q[c];
+        sides_known_ = true;
+    }
+
+    // Whether side stream i of the pool runs beside stream a, which is idle
+    // (see probe_wait_kernel). Waits for a, for at most the trial's time.
+    bool overlaps(hipStream_t a, size_t i) {
+        auto launch = [](auto* kernel, hipStream_t q, auto... args) {
+            void* p[] = {&args...};
+            WMI_HIP(hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(1), dim3(1), p, 0, q));
+        };
+        const int token = ++probe_token_;
+        *probe_seen_ = 0;
+        launch(&probe_set_kernel, side_pool_[i], probe_ + i, 0);  // the stream's first use may take longer
+        launch(&probe_wait_kernel, a, probe_ + i, token, probe_seen_);
+        launch(&probe_set_kernel, side_pool_[i], probe_ + i, token);
         WMI_HIP(hipStreamSynchronize(a));
-        WMI_HIP(hipStreamSynchronize(b));
         return *probe_seen_ != 0;
     }
 
     // Picks the side streams cst_[1 .. n_side_] for the context's stream: for
     // each the first of the pool, or a new one, that runs beside it and beside
     // the ones already picked; one that does not where none does (the work is
-    // the same then, without the overlap). A context's first stream after the
-    // own one shared its queue in one of four processes: 5 turbo segments took
-    // 28.1 instead of 17.1 ms, a small step of 33 rows 1.6 instead of 1.2 ms.
-    void choose_side_streams() {
-        constexpr size_t POOL = 6;  // streams tried at most
+    // the same then, without the overlap). Called when the context is made and
+    // by the first call on another stream that splits its work: choosing a
+    // stream stays as cheap as an assignment, and a stream's choice is
+    // remembered for the last KNOWN streams (a stream that took the handle of
+    // one destroyed may lose the overlap, nothing else). A trial takes some
+    // 40 us, up to 0.5 ms where the streams do not overlap, POOL of them at
+    // most per side stream. A context's first stream after the own one shared
+    // its queue in one of four processes: 5 turbo segments took 28.1 instead
+    // of 17.1 ms, a small step of 33 rows 1.6 instead of 1.2 ms.
+    void pick_side_streams() {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        WMI_HIP(hipStreamIsCapturing(st_, &cap));
+        if (cap != hipStreamCaptureStatusNone) return;
+        WMI_HIP(hipStreamSynchronize(st_));
+        Sides pick{};
+        bool sure = true;
         for (int c = 1; c <= n_side_; ++c) {
-            cst_[c] = nullptr;
             hipStream_t spare = nullptr;
-            for (size_t i = 0; i < POOL && !cst_[c]; ++i) {
+            for (size_t i = 0; i < POOL && !pick[c]; ++i) {
                 if (i == side_pool_.size()) {
                     hipStream_t q = nullptr;
                     WMI_HIP(hipStreamCreateWithFlags(&q, hipStreamNonBlocking));
                     side_pool_.push_back(q);
                 }
                 bool used = false, beside = true;
-                for (int k = 1; k < c; ++k) used = used || cst_[k] == side_pool_[i];
+                for (int k = 1; k < c; ++k) used = used || pick[k] == side_pool_[i];
                 if (used) continue;
                 if (!spare) spare = side_pool_[i];
-                for (int k = 0; k < c && beside; ++k) beside = overlaps(k == 0 ? st_ : cst_[k], side_pool_[i]);
-                if (beside) cst_[c] = side_pool_[i];
+                for (int k = 0; k < c && beside; ++k) beside = overlaps(k == 0 ? st_ : pick[k], i);
+                if (beside) pick[c] = side_pool_[i];
             }
-            if (!cst_[c]) cst_[c] = spare;
+            if (!pick[c]) {
+                pick[c] = spare;
+                sure = false;  // or the GPU was too busy: not remembered, tried again when the stream is chosen again
+            }
         }
+        use_sides(pick);
+        if (!sure) return;
+        if (known_sides_.size() < KNOWN) known_sides_.push_back({st_, pick});
+        else known_sides_[next_known_++ % KNOWN] = {st_, pick};
     }
 
     void sync() override {
@@ -413,6 +438,7 @@ class EngineT final : public Engine {
     void encode(const SegmentDesc* segs, int n, const int* slots, bool sync_) override {
         join_chains();
         WMI_HIP(hipSetDevice(dev_));
+        if (n > 1 && !sides_known_) pick_side_streams();
         for (int s0 = 0; s0 < n; s0 += EB_) encode_pass(segs + s0, std::min(EB_, n - s0), slots + s0);
         WMI_HIP(hipGetLastError());
         if (sync_) WMI_HIP(hipStreamSynchronize(st_));
@@ -463,6 +489,7 @@ class EngineT final : public Engine {
         // depends on the row count because the slot list lives in device memory.
         int r0[MAXC + 1];
         const int nc = timed ? (r0[0] = 0, r0[1] = n, 1) : chain_rows(n, r0);
+        if (nc > 1 && !sides_known_) pick_side_streams();
         auto stream = [&](int c) { return c == 0 ? st_ : cst_[c]; };
         prof_begin(WHISPER_K_DEC_STEP, st_);
         if (nc > 1) {  // fork: every chain waits for everything enqueued so far
@@ -959,6 +986,7 @@ class EngineT final : public Engine {
         WMI_HIP(hipSetDevice(dev_));
         if (!ctc_) throw ArgError(WHISPER_E_STATE, "not a CTC model");
         if (n < 1 || n > EB_) throw ArgError(WHISPER_E_INVAL, "encode_ctc: 1..max_encode_batch segments");
+        if (n > 1 && !sides_known_) pick_side_streams();
         const std::vector<int> none(n, 0);
         encode_pass(segs, n, none.data());
         WMI_HIP(hipGetLastError());
@@ -1108,11 +1136,15 @@ class EngineT final : public Engine {
     // side streams: decode chains 1.. and parts 1.. of an encoder pass (chain and part 0: st_)
     hipStream_t cst_[MAXC] = {};
     int n_side_ = 0;
-    bool side_picked_ = false;            // cst_ was tried out beside st_
-    std::vector<hipStream_t> side_pool_;  // every side stream made; cst_ points into it
-    // flag of overlaps(), and its answer in pinned host memory: a synchronous
-    // copy of it would wait for the program's other streams too
-    int *probe_ = nullptr, *probe_seen_ = nullptr;
+    static constexpr size_t POOL = 6, KNOWN = 16;
+    std::vector<hipStream_t> side_pool_;  // every side stream made, POOL at most; cst_ points into it
+    std::vector<std::pair<hipStream_t, Sides>> known_sides_;  // the streams' picks, KNOWN at most
+    size_t next_known_ = 0;
+    bool sides_known_ = false;  // cst_ was picked for st_
+    // flags of overlaps(), one per stream of the pool, and its answer in
+    // pinned host memory: a synchronous copy of it would wait for the
+    // program's other streams too
+    int *probe_ = nullptr, *probe_seen_ = nullptr, probe_token_ = 0;
     int enc_parts_ = 2;
     hipEvent_t fork_ev_ = nullptr, join_ev_[MAXC] = {};
     // host staging
