@@ -50,6 +50,9 @@ __device__ inline int swz32(int r, int c) { return r * 64 + ((c ^ ((r >> 1) & 3)
 
 // s_waitcnt immediate that waits until at most n vector-memory ops are outstanding.
 #define WMI_VMCNT(n) ((((n) & 0xF)) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
+// The same, and for every LDS read of this wave. A barrier does not wait for
+// them, and after it other waves' direct loads refill the buffer read last.
+#define WMI_VMCNT_LDS(n) (WMI_VMCNT(n) & ~(0xF << 8))
 
 // Byte offset of 16-byte chunk c (0..7) of row r inside a [rows][64] bf16 LDS tile.
 __device__ inline int swz(int r, int c) { return r * 128 + ((c ^ (r & 7)) << 4); }
@@ -337,8 +340,8 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_h_kernel(
     if (nk > 1) WMI_ISSUE3(1);
     for (int kt = 0; kt < nk; ++kt) {
         // tile kt has landed once only the 3-load group of the next tile is pending
-        if (kt + 1 < nk) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(3));
-        else __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
+        if (kt + 1 < nk) __builtin_amdgcn_s_waitcnt(WMI_VMCNT_LDS(3));
+        else __builtin_amdgcn_s_waitcnt(WMI_VMCNT_LDS(0));
         __builtin_amdgcn_s_barrier();
         if (kt + gh::NS - 1 < nk) WMI_ISSUE3(kt + gh::NS - 1);
         const unsigned char* stage = lds + (kt % gh::NS) * gh::STAGE_BYTES;
@@ -455,9 +458,9 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(const T* __restrict__
         // tile kt has landed once only the later tiles' 2 WT loads are pending
         const int later = min(nk - 1 - kt, NS - 2);
         static_assert((WT == 2 && NS <= 4) || NS == 2, "the waits below are literals");
-        if (later >= 2) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(8));
-        else if (later == 1) __builtin_amdgcn_s_waitcnt(WMI_VMCNT(4));
-        else __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
+        if (later >= 2) __builtin_amdgcn_s_waitcnt(WMI_VMCNT_LDS(8));
+        else if (later == 1) __builtin_amdgcn_s_waitcnt(WMI_VMCNT_LDS(4));
+        else __builtin_amdgcn_s_waitcnt(WMI_VMCNT_LDS(0));
         __builtin_amdgcn_s_barrier();
         if (kt + NS - 1 < nk) WMI_ISSUET(kt + NS - 1);
         const unsigned char* stage = lds + (kt % NS) * STAGE;

@@ -500,7 +500,7 @@ __global__ __launch_bounds__(256, 2) void enc_attn_bf16_kernel(const bf16* __res
     constexpr int ntiles = (N_CTX + ea::KT - 1) / ea::KT;
     issue(0);
     for (int kt = 0; kt < ntiles; ++kt) {
-        __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
+        __builtin_amdgcn_s_waitcnt(WMI_VMCNT_LDS(0));
         __builtin_amdgcn_s_barrier();  // tile kt is in LDS and every wave is done with tile kt - 1
         if (kt + 1 < ntiles) issue(kt + 1);
         const unsigned char* tk = lds + (kt & 1) * 2 * ea::TILE;
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(256, 2) void enc_attn_f32_kernel(const float* __res
     constexpr int ntiles = (N_CTX + ef::KT - 1) / ef::KT;
     issue(0);
     for (int kt = 0; kt < ntiles; ++kt) {
-        __builtin_amdgcn_s_waitcnt(WMI_VMCNT(0));
+        __builtin_amdgcn_s_waitcnt(WMI_VMCNT_LDS(0));
         __builtin_amdgcn_s_barrier();  // tile kt is in LDS and every wave is done with tile kt - 1
         if (kt + 1 < ntiles) issue(kt + 1);
         const unsigned char* tk = lds + (kt & 1) * 2 * ef::TILE;
