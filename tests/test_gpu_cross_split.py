@@ -57,3 +57,30 @@ def test_split_steps_equal_unsplit(name):
                     except binding.WhisperError as e:
                         assert e.status == binding.E_STATE
                         break
+
+
+@pytest.mark.parametrize("name,rows", [("base", [1, 2, 3, 4, 5, 6, 10]), ("large", [2, 4]), ("tiny", [1, 2, 5, 10, 11]),
+                                       ("wide", [1, 2, 3])])
+def test_allocation_free_split_steps_equal_regular_ones(name, rows):
+    """The allocation-free step keeps the chunks' results in the activations of
+    its MLP: as many rows as fit there (five of 16 in bf16, ten in fp32) are
+    split, on both sides of that limit. Two such steps, then the logits of a
+    regular one against three regular steps."""
+    shape = CASES[name][0].with_(n_enc=1, n_dec=2, n_vocab=1000)
+    W = synth.make_weights(shape, 0)
+    n = max(rows)
+    segs = synth.fixed_batch(shape, [16000 * (2 + i) for i in range(n)], 40, seed=62)
+    for i, seg in enumerate(segs):
+        seg.prompt = [1 + i]
+    with binding.Context(synth.pack_blob(W), max_slots=n) as a, binding.Context(synth.pack_blob(W), max_slots=n) as b:
+        a.encode(segs, list(range(n)))
+        b.encode(segs, list(range(n)))
+        for k in rows:
+            part = list(range(n - k, n))
+            for _ in range(2):
+                a.decode_step(part)
+                b.decode_step_noalloc(part)
+            ta, la = a.decode_step(part, logits=True)
+            tb, lb = b.decode_step(part, logits=True)
+            assert np.all(np.isfinite(la)) and np.array_equal(la, lb) and np.array_equal(ta, tb), (name, k)
+            print(f"{name}: {k} rows allocation-free: equal", flush=True)
