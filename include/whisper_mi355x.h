@@ -468,7 +468,10 @@ typedef enum {
     /* cross-attention of prefill rows; sizes: rows, heads, groups (up to 8 rows of one slot each);
        choice: 1 = a workgroup per group, 0 = a workgroup per row */
     WHISPER_CHOICE_PREFILL_CROSS = 1,
-    WHISPER_CHOICE_COUNT = 2
+    /* encoder GEMM; sizes: rows of both operands, reduction length, batch; choice: the tile's edge,
+       64, 128 or 256, or 384 for 256 x 128 */
+    WHISPER_CHOICE_ENC_GEMM = 2,
+    WHISPER_CHOICE_COUNT = 3
 } whisper_choice;
 
 /*

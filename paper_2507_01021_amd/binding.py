@@ -18,7 +18,7 @@ DTYPE_F32, DTYPE_BF16 = 0, 1
 T_MEL, T_ENC_OUT, T_CROSS_K, T_CROSS_V, T_CTC_LOGITS, T_CTC_IDS = 0, 1, 2, 3, 4, 5
 K_CROSS_ATTN, K_ENC_GEMM, K_SELF_ATTN, K_ENC_ATTN, K_ENC_PASS, K_DEC_STEP, K_FRONT_END = 0, 1, 2, 3, 4, 5, 6
 K_CROSS_ATTN_STEP = 7
-CHOICE_DEC_PROJ, CHOICE_PREFILL_CROSS = 0, 1
+CHOICE_DEC_PROJ, CHOICE_PREFILL_CROSS, CHOICE_ENC_GEMM = 0, 1, 2
 
 EXPORTS = (
     "whisper_params_from_blob", "whisper_ctx_create", "whisper_ctx_destroy", "whisper_last_error",

@@ -1677,6 +1677,12 @@ bool kernel_choice(int choice_of, int dtype, const int64_t* sizes, int n_sizes, 
         *choice = f32 ? share_rows<float>(n, H, g) : share_rows<bf16>(n, H, g);
         return true;
     }
+    if (choice_of == WHISPER_CHOICE_ENC_GEMM) {
+        if (n_sizes != 4) return false;
+        const int MA = (int)sizes[0], MB = (int)sizes[1], K = (int)sizes[2], batch = (int)sizes[3];
+        *choice = f32 ? gemm_f32_tile(MA, MB, batch) : gemm_bf16_tile(MA, MB, K, batch);
+        return true;
+    }
     return false;
 }
 

@@ -17,7 +17,7 @@
 //   128x128 and 64x64, chosen by the number of workgroups they give; a
 //   result's sum is the same in all of them. Tiles are mapped to the XCDs so
 //   that workgroups sharing an L2 share operand tiles.
-//   Requires K % 64 == 0, K >= 128, MA % 4 == 0, 16-byte aligned rows (lda, ldb % 8 == 0).
+//   Requires K % 64 == 0, MA % 4 == 0, 16-byte aligned rows (lda, ldb % 8 == 0).
 // gemm_f32: fp32 inputs on v_mfma_f32_16x16x4_f32 for the fp32 model, 64x64 or
 //   128x128 tiles. Requires K % 32 == 0 and 16-byte aligned rows.
 #pragma once
@@ -493,48 +493,66 @@ inline void gemm_tile(const T* A, int lda, long long sA, const T* B, int ldb, lo
                        A, lda, sA, B, ldb, sB, MA, MB, K, ta, epi);
 }
 
+// 128 x 128 tiles once they fill the chip's 512 workgroup slots (two per
+// CU); below that the 64 x 64 tiles' four times as many workgroups.
+inline int gemm_f32_tile(int MA, int MB, int batch) {
+    return (long long)((MA + 127) / 128) * ((MB + 127) / 128) * batch >= 512 ? 128 : 64;
+}
+
 template <class Epi>
 inline void gemm_f32(const float* A, int lda, long long sA, const float* B, int ldb, long long sB, int MA, int MB,
                      int K, int batch, const Epi& epi, hipStream_t st) {
     // rows i0..i0+3 past MA reach the epilogue when MA % 4 != 0: it must drop them
     if (MA <= 0 || MB <= 0 || K <= 0 || K % 32 || lda % 4 || ldb % 4 || sA % 4 || sB % 4 || batch <= 0)
         throw ArgError(-1, "gemm_f32: unsupported shape");
-    // 128 x 128 tiles once they fill the chip's 512 workgroup slots (two per
-    // CU); below that the 64 x 64 tiles' four times as many workgroups.
-    if ((long long)((MA + 127) / 128) * ((MB + 127) / 128) * batch >= 512)
+    if (gemm_f32_tile(MA, MB, batch) == 128)
         gemm_tile<float, 4, 2>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
     else
         gemm_tile<float, 2, 4>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
 }
 
-template <class Epi>
-inline void gemm_bf16(const bf16* A, int lda, long long sA, const bf16* B, int ldb, long long sB,
-                      int MA, int MB, int K, int batch, const Epi& epi, hipStream_t st) {
-    if (K % 64 || K < 128 || MA % 4 || lda % 8 || ldb % 8 || MA <= 0 || MB <= 0 || batch <= 0)
-        throw ArgError(-1, "gemm_bf16: unsupported shape");
-    // The tile by the number of workgroups it gives 256 CUs (measured alone
-    // on the encoder's launches of 1 to 32 segments, d = 512, 768 and 1280):
-    //  - 64 x 64 while 128 x 128 tiles are fewer than 144 (d = 1280, one
-    //    segment, fc2: 36.5 us against 56.4 with 128, 102.7 with 256);
-    //  - 256 x 256, one per CU, if they fit one round and fill at least 144
-    //    CUs (d = 1280, 5 segments, fc2, 150 tiles: 106 against 130 us with
-    //    128; 4 segments, 120 tiles: 105 against 84), or if their rounds are
-    //    at least 75 % full (70 % for K >= 2048, where they gain most; d = 768,
-    //    32 segments, 73 % full: fc2 268 against 306 us, V 77.6 against 75.6);
-    //  - for K <= 640 with at least 750 of them, 256 x 128, two per CU (d = 512,
-    //    16 segments, QK: 38.5 against 41.7 us with 128);
-    //  - 128 x 128, two per CU, otherwise.
-    // WHISPER_GEMM_TILE = 64, 128, 256 or 384 (256 x 128) forces one.
-    static const int force = [] {
-        const char* g = getenv("WHISPER_GEMM_TILE");
-        return g ? atoi(g) : 0;
-    }();
+// The tile by the number of workgroups it gives 256 CUs (measured alone
+// on the encoder's launches of 1 to 32 segments, d = 512, 768 and 1280):
+//  - 64 x 64 while 128 x 128 tiles are fewer than 144 (d = 1280, one
+//    segment, fc2: 36.5 us against 56.4 with 128, 102.7 with 256);
+//  - 256 x 256, one per CU, if they fit one round and fill at least 144
+//    CUs (d = 1280, 5 segments, fc2, 150 tiles: 106 against 130 us with
+//    128; 4 segments, 120 tiles: 105 against 84), or if their rounds are
+//    at least 75 % full (70 % for K >= 2048, where they gain most; d = 768,
+//    32 segments, 73 % full: fc2 268 against 306 us, V 77.6 against 75.6),
+//    for K >= 128, the two K tiles its loop needs;
+//  - for K <= 640 with at least 750 of them, 256 x 128, two per CU (d = 512,
+//    16 segments, QK: 38.5 against 41.7 us with 128);
+//  - 128 x 128, two per CU, otherwise.
+// Returns 64, 128, 256 or 384 (256 x 128).
+inline int gemm_bf16_tile(int MA, int MB, int K, int batch) {
     const int tilesA = (MA + gb::BM - 1) / gb::BM, tilesB = (MB + gb::BN - 1) / gb::BN;
     const long long t128 = (long long)((MA + 127) / 128) * ((MB + 127) / 128) * batch;
     const long long t384 = (long long)tilesA * ((MB + gh::BN - 1) / gh::BN) * batch;
     const long long t256 = (long long)tilesA * tilesB * batch;
     const bool big = t256 <= 256 ? t256 >= 144 : t256 * 100 >= (t256 + 255) / 256 * 256 * (K >= 2048 ? 70 : 75);
-    const int tile = force ? force : t128 < 144 ? 64 : big ? 256 : K <= 640 && t384 >= 750 ? 384 : 128;
+    return t128 < 144 ? 64 : big && K >= 128 ? 256 : K <= 640 && t384 >= 750 ? 384 : 128;
+}
+
+template <class Epi>
+inline void gemm_bf16(const bf16* A, int lda, long long sA, const bf16* B, int ldb, long long sB,
+                      int MA, int MB, int K, int batch, const Epi& epi, hipStream_t st) {
+    if (K <= 0 || K % 64 || MA % 4 || lda % 8 || ldb % 8 || MA <= 0 || MB <= 0 || batch <= 0)
+        throw ArgError(-1, "gemm_bf16: unsupported shape");
+    // WHISPER_GEMM_TILE = 64, 128, 256 or 384 forces one tile; the older
+    // WHISPER_GEMM_H = 1 or 0 stands for 384 or 256.
+    static const int force = [] {
+        if (const char* g = getenv("WHISPER_GEMM_TILE")) {
+            const int t = atoi(g);
+            if (t != 64 && t != 128 && t != 256 && t != 384)
+                throw ArgError(-1, "WHISPER_GEMM_TILE must be 64, 128, 256 or 384");
+            return t;
+        }
+        if (const char* g = getenv("WHISPER_GEMM_H")) return g[0] == '1' ? 384 : 256;
+        return 0;
+    }();
+    const int tile = force && (force != 256 || K >= 128) ? force : gemm_bf16_tile(MA, MB, K, batch);
+    const int tilesA = (MA + gb::BM - 1) / gb::BM, tilesB = (MB + gb::BN - 1) / gb::BN;
     if (tile == 64) return gemm_tile<bf16, 2, 4>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
     if (tile == 128) return gemm_tile<bf16, 4, 2>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
     if (tile == 384) {

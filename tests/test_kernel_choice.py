@@ -71,6 +71,26 @@ def test_long_prompts_share_their_slots_rows(dtype):
             assert shared(dtype, slots, min(per, 2048 // slots), H) == 1, (H, slots)
 
 
+def tile(MA, MB, K, batch=1, dtype=DTYPE_BF16):
+    return binding.test_kernel_choice(binding.CHOICE_ENC_GEMM, dtype, MA, MB, K, batch)
+
+
+def test_gemm_tiles():
+    # a 128 x 128 tile for 144 of them, 64 x 64 below
+    assert tile(128 * 12, 128 * 11, 1280) == 64 and tile(128 * 12, 128 * 12, 1280) == 128
+    # one round of 256 x 256 from 144 tiles on
+    assert tile(256 * 11, 256 * 13, 1280) == 128 and tile(256 * 12, 256 * 12, 1280) == 256
+    # further rounds 75 % full (70 % for long reductions): 384 and 359 of 512
+    assert tile(256 * 24, 256 * 16, 1280) == 256 and tile(256 * 383, 256, 1280) == 128
+    assert tile(256 * 359, 256, 2048) == 256 and tile(256 * 358, 256, 2048) == 128
+    # short reductions: 750 tiles of 256 x 128
+    assert tile(256, 128 * 749, 640) == 128 and tile(256, 128 * 750, 640) == 384
+    assert tile(256, 128 * 750, 704) == 128
+    # the 256 x 256 kernel needs two K tiles
+    assert tile(256 * 16, 256 * 16, 128) == 256 and tile(256 * 16, 256 * 16, 64) == 128
+    assert tile(128 * 22, 128 * 23, 384, dtype=DTYPE_F32) == 64 and tile(128 * 32, 128 * 16, 384, dtype=DTYPE_F32) == 128
+
+
 def test_bad_choice_arguments_are_refused():
     for args in [(binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 0, 4), (binding.CHOICE_DEC_PROJ, DTYPE_F32, 1280, 1, 1, 8),
                  (binding.CHOICE_DEC_PROJ, 2, 1280, 1, 1, 4), (binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 1), (99, 0, 1)]:
