@@ -511,18 +511,20 @@ inline void gemm_f32(const float* A, int lda, long long sA, const float* B, int 
         gemm_tile<float, 2, 4>(A, lda, sA, B, ldb, sB, MA, MB, K, batch, epi, st);
 }
 
-// The tile by the number of workgroups it gives 256 CUs (measured alone
-// on the encoder's launches of 1 to 32 segments, d = 512, 768 and 1280):
-//  - 64 x 64 while 128 x 128 tiles are fewer than 144 (d = 1280, one
-//    segment, fc2: 36.5 us against 56.4 with 128, 102.7 with 256);
-//  - 256 x 256, one per CU, if they fit one round and fill at least 144
-//    CUs (d = 1280, 5 segments, fc2, 150 tiles: 106 against 130 us with
-//    128; 4 segments, 120 tiles: 105 against 84), or if their rounds are
-//    at least 75 % full (70 % for K >= 2048, where they gain most; d = 768,
-//    32 segments, 73 % full: fc2 268 against 306 us, V 77.6 against 75.6),
-//    for K >= 128, the two K tiles its loop needs;
-//  - for K <= 640 with at least 750 of them, 256 x 128, two per CU (d = 512,
-//    16 segments, QK: 38.5 against 41.7 us with 128);
+// The tile by the number of workgroups it gives 256 CUs. Measured on whole
+// passes of 1 to 32 segments at widths 512 to 2048 as they run, the two halves
+// of a pass side by side, so that one half's workgroups fill the CUs that the
+// other's last round leaves idle (pass times in us):
+//  - 64 x 64 while 128 x 128 tiles are fewer than 144 (100: d = 1280, 1
+//    segment 16 % slower; 200: d = 2048, 2 segments 9 % slower);
+//  - 256 x 256, one per CU, from 144 tiles on (128 the same, 176 and 112 up to
+//    4 % slower), unless K < 2048 and the rounds of more than one are less
+//    than 60 % full (d = 768, 8 segments 4 % slower without this; a line at
+//    75 %, right for a launch alone, lost 7 % at d = 1536, 20 segments, and d =
+//    2048, 14 segments), and K >= 128, the two K tiles its loop needs;
+//  - for K <= 640 (line at 75 %) with at least 750 of them, 256 x 128, two per
+//    CU (alone, d = 512, 16 segments, QK: 38.5 against 41.7 us with 128; whole
+//    passes at d = 384 and 512 measure the same with either, within 2 %);
 //  - 128 x 128, two per CU, otherwise.
 // Returns 64, 128, 256 or 384 (256 x 128).
 inline int gemm_bf16_tile(int MA, int MB, int K, int batch) {
@@ -530,7 +532,8 @@ inline int gemm_bf16_tile(int MA, int MB, int K, int batch) {
     const long long t128 = (long long)((MA + 127) / 128) * ((MB + 127) / 128) * batch;
     const long long t384 = (long long)tilesA * ((MB + gh::BN - 1) / gh::BN) * batch;
     const long long t256 = (long long)tilesA * tilesB * batch;
-    const bool big = t256 <= 256 ? t256 >= 144 : t256 * 100 >= (t256 + 255) / 256 * 256 * (K >= 2048 ? 70 : 75);
+    const bool big = t256 >= 144 && (t256 <= 256 || K >= 2048 ||
+                                     t256 * 100 >= (t256 + 255) / 256 * 256 * (K <= 640 ? 75 : 60));
     return t128 < 144 ? 64 : big && K >= 128 ? 256 : K <= 640 && t384 >= 750 ? 384 : 128;
 }
 

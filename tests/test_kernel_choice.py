@@ -80,12 +80,13 @@ def test_gemm_tiles():
     assert tile(128 * 12, 128 * 11, 1280) == 64 and tile(128 * 12, 128 * 12, 1280) == 128
     # one round of 256 x 256 from 144 tiles on
     assert tile(256 * 11, 256 * 13, 1280) == 128 and tile(256 * 12, 256 * 12, 1280) == 256
-    # further rounds 75 % full (70 % for long reductions): 384 and 359 of 512
-    assert tile(256 * 24, 256 * 16, 1280) == 256 and tile(256 * 383, 256, 1280) == 128
-    assert tile(256 * 359, 256, 2048) == 256 and tile(256 * 358, 256, 2048) == 128
-    # short reductions: 750 tiles of 256 x 128
+    # further rounds 60 % full, 308 of 512, unless the reduction is long
+    assert tile(256 * 308, 256, 1280) == 256 and tile(256 * 307, 256, 1280) == 128
+    assert tile(256 * 307, 256, 2047) == 128 and tile(256 * 257, 256, 2048) == 256
+    # short reductions: 75 % full, 384 of 512, else 750 tiles of 256 x 128
     assert tile(256, 128 * 749, 640) == 128 and tile(256, 128 * 750, 640) == 384
-    assert tile(256, 128 * 750, 704) == 128
+    assert tile(256 * 384, 256, 640) == 256 and tile(256 * 383, 256, 640) == 384
+    assert tile(256, 128 * 750, 704) == 256
     # the 256 x 256 kernel needs two K tiles
     assert tile(256 * 16, 256 * 16, 128) == 256 and tile(256 * 16, 256 * 16, 64) == 128
     assert tile(128 * 22, 128 * 23, 384, dtype=DTYPE_F32) == 64 and tile(128 * 32, 128 * 16, 384, dtype=DTYPE_F32) == 128
