@@ -361,7 +361,8 @@ whisper_status whisper_debug_copy(whisper_ctx* ctx, int32_t tensor, int32_t inde
 /* Kernels that can be timed live with HIP events (on the stream they are
  * launched on): every launch between enable and read is bracketed. */
 enum {
-    WHISPER_K_CROSS_ATTN = 0,  /* decode-step cross-attention over the cache */
+    WHISPER_K_CROSS_ATTN = 0,  /* decode-step cross-attention over the cache (steps of few rows: of its
+                                  chunks, whose merge is part of the output projection) */
     WHISPER_K_ENC_GEMM = 1,    /* encoder fc1 GEMM (bf16 MFMA) */
     WHISPER_K_SELF_ATTN = 2,   /* decode-step self-attention */
     WHISPER_K_ENC_ATTN = 3,    /* encoder attention */
@@ -384,7 +385,8 @@ whisper_status whisper_profile_enable(whisper_ctx* ctx, int32_t kernel, int32_t 
  * events on the context's stream (synchronises it). Only
  * WHISPER_K_CROSS_ATTN (the decode cross-attention of Section 2.3's batched
  * decoder: each launch reads the cached encoder keys and values of n_rows
- * slots x all heads, layer i mod the decoder depth for launch i). The slots'
+ * slots x all heads, layer i mod the decoder depth for launch i; always the
+ * kernel of whole rows, also for the few rows that a step splits). The slots'
  * caches are read as they are (encode them first for meaningful data) and
  * the step's attention output buffer is overwritten; call it between decode
  * steps, not during a transcribe call. Errors: WHISPER_E_INVAL for another

@@ -699,7 +699,8 @@ class EngineT final : public Engine {
         L.dh = take(n16 * 4 * d * sizeof(T));
         L.part = take((size_t)KSMAX * n * d * sizeof(float));
         L.keys = take((size_t)n * nkeys_ * sizeof(unsigned long long));
-        // the documented capacity of the fp32 model counts the rows' logits
+        // the capacity of the fp32 model counts the rows' logits: nothing writes
+        // them any more, but sizes that were refused stay refused
         L.logits = std::is_same<T, bf16>::value ? o : take((size_t)n * V_ * sizeof(float));
         L.end = o;
         return L;
@@ -1589,7 +1590,7 @@ class EngineT final : public Engine {
         vs_ = dalloc<T>(Ld * S * H * TS * 64);
         ktc_ = dalloc<T>(Ld * S * H * 64 * TC);
         vc_ = dalloc<T>(Ld * S * H * TC * 64);
-        // activations multiplied by projections: whole 16-row tiles (fragment-major in bf16)
+        // activations multiplied by projections: whole 16-row tiles (fragment-major)
         const size_t S16 = (S + 15) / 16 * 16;
         dx_ = dalloc<float>(S * d);
         dz_ = dalloc<T>(S16 * d);

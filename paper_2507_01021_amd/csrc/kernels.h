@@ -1977,7 +1977,7 @@ template <class T, class Epi>
 inline void skinny_merge(const T* W, int MA, const CrossPart& x, int H, int n, int K, int KS, const Epi& epi,
                          hipStream_t st) {
     const int Kc = K / KS, nks = Kc / KSTEP<T>;
-    if (KS < 1 || K % (KSTEP<T> * KS) || n <= 0 || n > 16 || MA <= 0 || nks > 64)
+    if (KS < 1 || K % (KSTEP<T> * KS) || n <= 0 || n > 16 || MA <= 0 || nks > 32)
         throw ArgError(-1, "skinny_merge: unsupported shape");
     const dim3 grid((MA + 15) / 16, KS);
     auto launch = [&](auto u) {
@@ -1987,8 +1987,7 @@ inline void skinny_merge(const T* W, int MA, const CrossPart& x, int H, int n, i
     const int u = (nks + 3) / 4;
     if (u <= 2) launch(std::integral_constant<int, 2>{});
     else if (u <= 4) launch(std::integral_constant<int, 4>{});
-    else if (u <= 8) launch(std::integral_constant<int, 8>{});
-    else launch(std::integral_constant<int, 16>{});
+    else launch(std::integral_constant<int, 8>{});  // 32 k-steps: width 2048 in fp32, a quarter of K
 }
 
 // ------------------------------------------------------------- CTC greedy decoding
