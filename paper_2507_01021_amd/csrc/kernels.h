@@ -1253,8 +1253,10 @@ __global__ __launch_bounds__(128) void cross_attn_split_kernel(DecAttnArgs a, Cr
 // them (one row at a time, 223 prompt positions read 384 KB per head 223
 // times). Every result is computed with cross_attn_kernel's operations in
 // its order, so a prefilled position equals a stepped one bit for bit; a
-// row's query sits one dim per lane and is broadcast by readlane. With 8
-// rows the kernel is bound by its fp32 FMAs, not by the caches' bytes: 3568
+// row's query sits one dim per lane and is broadcast by readlane. Bound by
+// load latency at low occupancy: a CU holds one workgroup (1.4 waves per
+// SIMD), whose vector instructions take half of the cycles while its waves
+// wait a third of theirs; the caches' bytes come from L2 (92 % hits). 3568
 // rows x 12 heads take 0.66 ms per layer, one row per workgroup 2.04 ms.
 constexpr int XR = 8;
 
@@ -1731,10 +1733,12 @@ constexpr int skinny_u(int nks) {
 // skinny_core's NW waves one after another, adding each sequence's sum to the
 // total in their order, so that a result is the same bit for bit while every
 // loaded fragment feeds two or four MFMAs and every wave has an epilogue of
-// its own. Bound by the L1's 64 bytes per clock (24 KB of fragments per
-// k-step and workgroup against 128 MFMA cycles). 3568 rows, d = 768: a
-// layer's two split-K projections take 86 us, as 28 chunks of 128 rows in
-// skinny_kernel 377 us.
+// its own. Bound by load latency: 1 to 2 waves per SIMD wait in 54-76 % of
+// their time, the matrix cores are busy 3-12 %, the L1 serves 0.3-0.45
+// transactions per clock. 3568 rows, d = 768: a layer's two split-K
+// projections (o in 4, fc2 in 8 parts) take 86 us, as 28 chunks of 128 rows
+// in skinny_kernel 377 us; their partials, 72 MB written for 2048 rows, are
+// read back by resid_ln_kernel.
 template <class T, int NW, class Epi>
 __global__ __launch_bounds__(256) void many_kernel(const T* __restrict__ W, const T* __restrict__ X, int nks_tot, int n,
                                                    int Kc, Epi epi) {
