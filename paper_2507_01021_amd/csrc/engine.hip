@@ -361,7 +361,8 @@ class EngineT final : public Engine {
             if (k.first == st_) use_sides(k.second);
     }
 
-    typedef std::array<hipStream_t, 4> Sides;  // [1 .. n_side_] used
+    static constexpr int MAXC = 4;  // chains of a step, parts of a pass (hardware queues)
+    typedef std::array<hipStream_t, MAXC> Sides;  // [1 .. n_side_] used
     void use_sides(const Sides& q) {
         for (int c = 1; c <= n_side_; ++c) cst_[c] = q[c];
         sides_known_ = true;
@@ -1127,7 +1128,6 @@ class EngineT final : public Engine {
     int ctc_ticket_ = 0;
     hipStream_t ctc_st_ = nullptr;  // beam search of one batch beside the next batch's encoder
     hipEvent_t ctc_head_[2] = {}, ctc_done_[2] = {};
-    static constexpr int MAXC = 4;                                  // chains of a step (hardware queues)
     int chains_ = 2;
     std::map<int, std::array<hipGraphExec_t, MAXC>> step_graphs_;  // per row count: one graph per chain
     std::map<int, std::array<hipGraphExec_t, MAXC>> stamped_graphs_;  // the same with cross-attention stamps
