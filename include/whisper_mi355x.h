@@ -479,8 +479,8 @@ typedef enum {
 /*
  * Host-only check of the engine's dispatch (no device work): the variant
  * that a launch of the given sizes takes in a model of type `dtype`
- * (whisper_dtype). sizes: host array of n_sizes values as listed at
- * `choice_of` (whisper_choice); *choice receives the variant. Errors:
+ * (whisper_dtype). sizes: host array of n_sizes values (1 .. 2^20) as
+ * listed at `choice_of` (whisper_choice); *choice receives the variant. Errors:
  * WHISPER_E_INVAL.
  */
 whisper_status whisper_test_kernel_choice(int32_t choice_of, int32_t dtype, const int64_t* sizes,

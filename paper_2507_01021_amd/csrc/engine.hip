@@ -1664,7 +1664,7 @@ bool kernel_choice(int choice_of, int dtype, const int64_t* sizes, int n_sizes, 
     if (dtype != WHISPER_DTYPE_F32 && dtype != WHISPER_DTYPE_BF16) return false;
     const bool f32 = dtype == WHISPER_DTYPE_F32;
     for (int i = 0; i < n_sizes; ++i)
-        if (sizes[i] < 1 || sizes[i] > INT32_MAX) return false;
+        if (sizes[i] < 1 || sizes[i] > 1 << 20) return false;
     if (choice_of == WHISPER_CHOICE_DEC_PROJ) {
         if (n_sizes != 4 || (sizes[3] != 4 && sizes[3] != RESID_NW) || (f32 && sizes[3] != 4)) return false;
         const int MA = (int)sizes[0], KS = (int)sizes[1], n = (int)sizes[2];

@@ -94,7 +94,8 @@ def test_gemm_tiles():
 
 def test_bad_choice_arguments_are_refused():
     for args in [(binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 0, 4), (binding.CHOICE_DEC_PROJ, DTYPE_F32, 1280, 1, 1, 8),
-                 (binding.CHOICE_DEC_PROJ, 2, 1280, 1, 1, 4), (binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 1), (99, 0, 1)]:
+                 (binding.CHOICE_DEC_PROJ, 2, 1280, 1, 1, 4), (binding.CHOICE_DEC_PROJ, DTYPE_BF16, 1280, 1, 1), (99, 0, 1),
+                 (binding.CHOICE_ENC_GEMM, DTYPE_BF16, (1 << 20) + 1, 256, 256, 1)]:
         with pytest.raises(binding.WhisperError) as e:
             binding.test_kernel_choice(*args)
         assert e.value.status == binding.E_INVAL
